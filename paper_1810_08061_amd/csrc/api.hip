@@ -106,8 +106,9 @@ struct lstm_dyn {
     void* block;               // the one device allocation behind ws
     int32_t* host_maxlen;      // pinned host words for the per-step path: [0] loop bound,
                                // [1] rows still running, [2] iterations run
-    int stop_ok;               // the persistent variant with termination from the state fits
-    int save_ok;               // the persistent variant of the forward for training fits
+    XLoopConfig xl[3];         // by LoopMode: the XCD-grouped loop, or variant null: the device-wide one
+    int stop_ok;               // a persistent variant with termination from the state fits
+    int save_ok;               // a persistent variant of the forward for training fits
     TrainWs* train;            // null until the first forward for training
     int saved;                 // 1: the workspace holds a forward for training not yet used
     unsigned long long timeout_ticks;
@@ -133,10 +134,11 @@ long long align_up(long long v, long long a) { return (v + a - 1) / a * a; }
 
 
 struct Layout {
-    long long meta, perm, offsets, rowsrc, gx, hx, bar, z, wt, w4, u4, b4, stopped, running, total;
+    long long meta, perm, offsets, rowsrc, gx, hx, bar, z, wt, w4, u4, b4, stopped, running, ux, total;
 };
 
-Layout layout_of(int B, int D, int H, int T, int bf16, int mode, int bpad, int hpad, int packed = 0) {
+Layout layout_of(int B, int D, int H, int T, int bf16, int mode, int bpad, int hpad, int packed,
+                 long long ux_bytes) {
     Layout L{};
     long long o = 0;
     auto take = [&](long long bytes) {
@@ -166,6 +168,7 @@ Layout layout_of(int B, int D, int H, int T, int bf16, int mode, int bpad, int h
     L.b4 = take(packed ? 16LL * H : 0);
     L.stopped = take(4LL * B);
     L.running = take(4LL * T);
+    L.ux = take(ux_bytes);
     L.total = o;
     return L;
 }
@@ -194,8 +197,9 @@ namespace ldyn {
 // operand buffer's offset and size (the only part that must start at zero
 // on every forward: its padding columns are multiplied by zero weights).
 long long carve_forward_workspace(const Dims& d, char* base, Workspace* ws, long long* hx_off,
-                                  long long* hx_bytes) {
-    const Layout L = layout_of(d.B, d.D, d.H, d.T, d.bf16, LSTM_DYN_PERSISTENT, d.bpad, d.hpad, 0);
+                                  long long* hx_bytes, long long ux_bytes) {
+    const Layout L =
+        layout_of(d.B, d.D, d.H, d.T, d.bf16, LSTM_DYN_PERSISTENT, d.bpad, d.hpad, 0, ux_bytes);
     *hx_off = L.hx;
     *hx_bytes = L.bar - L.hx;
     if (base) {
@@ -210,8 +214,22 @@ long long carve_forward_workspace(const Dims& d, char* base, Workspace* ws, long
         ws->wt = d.bf16 ? base + L.wt : nullptr;
         ws->stopped = reinterpret_cast<int32_t*>(base + L.stopped);
         ws->running = reinterpret_cast<int32_t*>(base + L.running);
+        ws->ux = ux_bytes ? base + L.ux : nullptr;
     }
     return L.total;
+}
+
+// The loop's two forms.
+bool xloop_for(const Dims& d, int mode, int num_cus, XLoopConfig* xc) {
+    if (xloop_pick(d, num_cus, xc) && xloop_fits(d, *xc, mode, num_cus)) return true;
+    *xc = XLoopConfig{};
+    return false;
+}
+hipError_t launch_loop(const Dims& d, const XLoopConfig& xc, const PersistentConfig& pc, const void* U,
+                       const float* h0, const float* c0, float* out_h, float* out_c,
+                       const Workspace& ws, hipStream_t s) {
+    return xc.variant ? launch_xloop(d, xc, pc, U, h0, c0, out_h, out_c, ws, s)
+                      : launch_persistent(d, pc, U, h0, c0, out_h, out_c, ws, s);
 }
 }  // namespace ldyn
 
@@ -267,13 +285,16 @@ extern "C" int lstm_dyn_plan(int B, int D, int H, int T, int dtype, int mode, in
     out->bpad = ntmax * 16;
     out->lds_bytes = persistent_lds_bytes(bf16, mt, kw, nst, out->hpad);
     out->nstate = nst;
-    out->workspace_bytes =
-        layout_of(B, D, H, T, bf16, mode, out->bpad, out->hpad).total;
     if (mode == LSTM_DYN_PERSISTENT && H <= 32 &&
         small_pick(bf16, B, D, H, &out->single_kd, &out->single_nt)) {
         out->single = 1;
         out->groups = 1;
     }
+    XLoopConfig xc{};
+    if (mode == LSTM_DYN_PERSISTENT && !out->single)
+        (void)xloop_pick(Dims{B, D, H, T, bf16, out->hpad, out->bpad, CELL_LSTM}, num_cus, &xc);
+    out->workspace_bytes =
+        layout_of(B, D, H, T, bf16, mode, out->bpad, out->hpad, 0, xc.ux_bytes).total;
     return LSTM_DYN_OK;
 }
 
@@ -382,27 +403,33 @@ extern "C" int lstm_dyn_create_cell(lstm_dyn_t** out, int B, int D, int H, int T
     if (rc != LSTM_DYN_OK) return rc;
     const int bf16 = dtype == LSTM_DYN_BF16;
     int stop_ok = 1, save_ok = 1;
+    XLoopConfig xl[3] = {};
     if (mode == LSTM_DYN_PERSISTENT && !plan.single) {
-        const int per_cu = persistent_blocks_per_cu(bf16, plan.mt, plan.ksw, plan.kw, plan.nstate,
-                                                    plan.lds_bytes, cell, 0);
-        if (per_cu < 1 || plan.groups > per_cu * cus) return LSTM_DYN_ERR_UNSUPPORTED;
-        const int per_cu_stop = persistent_blocks_per_cu(bf16, plan.mt, plan.ksw, plan.kw,
-                                                         plan.nstate, plan.lds_bytes, cell, 1);
-        stop_ok = per_cu_stop >= 1 && plan.groups <= per_cu_stop * cus;
-        const int per_cu_save = persistent_blocks_per_cu(bf16, plan.mt, plan.ksw, plan.kw,
-                                                         plan.nstate, plan.lds_bytes, cell, 2);
-        save_ok = per_cu_save >= 1 && plan.groups <= per_cu_save * cus;
+        // each mode takes the XCD-grouped loop where it applies, else the device-wide one
+        auto loop_ok = [&](int m) {
+            if (xloop_for(Dims{B, D, H, T, bf16, plan.hpad, plan.bpad, cell}, m, cus, &xl[m])) return true;
+            const int per_cu = persistent_blocks_per_cu(bf16, plan.mt, plan.ksw, plan.kw, plan.nstate,
+                                                        plan.lds_bytes, cell, m);
+            return per_cu >= 1 && plan.groups <= per_cu * cus;
+        };
+        if (!loop_ok(0)) return LSTM_DYN_ERR_UNSUPPORTED;
+        stop_ok = loop_ok(1);
+        save_ok = loop_ok(2);
     }
     lstm_dyn* h = new (std::nothrow) lstm_dyn();
     if (!h) return LSTM_DYN_ERR_NOMEM;
     h->B = B; h->D = D; h->H = H; h->T = T; h->dtype = dtype; h->mode = mode; h->cell = cell;
+    for (int m = 0; m < 3; ++m) h->xl[m] = xl[m];
     h->stop_ok = stop_ok;
     h->save_ok = save_ok;
     h->device = dev;
     h->num_cus = cus;
     h->plan = plan;
     h->dims = Dims{B, D, H, T, bf16, plan.hpad, plan.bpad, cell};
-    const Layout L = layout_of(B, D, H, T, bf16, mode, plan.bpad, plan.hpad, packed);
+    long long ux_bytes = 0;
+    for (const XLoopConfig& xc : xl)
+        if (xc.variant) ux_bytes = xc.ux_bytes;
+    const Layout L = layout_of(B, D, H, T, bf16, mode, plan.bpad, plan.hpad, packed, ux_bytes);
     h->workspace = L.total;
     if (hipMalloc(&h->block, (size_t)L.total) != hipSuccess) {
         (void)hipGetLastError();
@@ -424,6 +451,7 @@ extern "C" int lstm_dyn_create_cell(lstm_dyn_t** out, int B, int D, int H, int T
     h->b4 = packed ? reinterpret_cast<float*>(base + L.b4) : nullptr;
     h->ws.stopped = reinterpret_cast<int32_t*>(base + L.stopped);
     h->ws.running = reinterpret_cast<int32_t*>(base + L.running);
+    h->ws.ux = ux_bytes ? base + L.ux : nullptr;
     // Zero the small tables and the operand buffer (its padding must stay zero).
     if (hipMemset(base, 0, (size_t)L.gx) != hipSuccess ||
         hipMemset(base + L.hx, 0, (size_t)(L.total - L.hx)) != hipSuccess) {
@@ -594,7 +622,7 @@ static int forward_impl(lstm_dyn_t* h, const void* x, const int32_t* lengths, co
         }
         return LSTM_DYN_OK;
     }
-    LD_CHECK(launch_prep(d, lengths, h->ws, s));
+    LD_CHECK(launch_prep(d, lengths, h->ws, s, stop != nullptr, U, &h->xl[stop ? 1 : 0]));
     h->launches_last += 1 + pack_launches;
     LD_CHECK(mark(1));
     if (h->mode == LSTM_DYN_PERSISTENT) {
@@ -603,7 +631,7 @@ static int forward_impl(lstm_dyn_t* h, const void* x, const int32_t* lengths, co
         PersistentConfig pc{h->plan.mt,     h->plan.groups,    h->plan.ksw, h->plan.kw,
                             h->plan.nstate, h->plan.lds_bytes, h->timeout_ticks, h->trace,
                             out_seq,        stop};
-        LD_CHECK(launch_persistent(d, pc, U, h0, c0, out_h, out_c, h->ws, s));
+        LD_CHECK(launch_loop(d, h->xl[stop ? 1 : 0], pc, U, h0, c0, out_h, out_c, h->ws, s));
         h->launches_last++;
         LD_CHECK(mark(3));
         if (out_seq) {  // the loop wrote the valid steps; zeros past each row's last
@@ -877,7 +905,7 @@ extern "C" int lstm_dyn_forward_train(lstm_dyn_t* h, const void* x, const int32_
         b = h->b4;
         h->launches_last++;
     }
-    LD_CHECK(launch_prep(d, lengths, h->ws, s));
+    LD_CHECK(launch_prep(d, lengths, h->ws, s, false, U, &h->xl[2]));
     LD_CHECK(mark(1));
     h->launches_last++;
     if (h->mode == LSTM_DYN_PERSISTENT && !h->plan.single && h->save_ok) {
@@ -886,7 +914,7 @@ extern "C" int lstm_dyn_forward_train(lstm_dyn_t* h, const void* x, const int32_
         PersistentConfig pc{h->plan.mt,     h->plan.groups,    h->plan.ksw, h->plan.kw,
                             h->plan.nstate, h->plan.lds_bytes, h->timeout_ticks, h->trace,
                             nullptr,        nullptr,           tw->save_h,  tw->save_c};
-        LD_CHECK(launch_persistent(d, pc, U, h0, c0, out_h, out_c, h->ws, s));
+        LD_CHECK(launch_loop(d, h->xl[2], pc, U, h0, c0, out_h, out_c, h->ws, s));
         h->launches_last++;
     } else {
         // the per-step kernels (single-workgroup sizes, per-step handles)

@@ -105,7 +105,9 @@ struct EltH16 {
 
 // ---------------------------------------------------------------------------
 // Gate non-linearities in fp32 from the hardware exp2 and reciprocal.
-// sigmoid(0) and tanh(0) come out exactly 1/2 and 0.
+// sigmoid(0) and tanh(0) come out exactly 1/2 and 0.  The cells' fused
+// multiply-adds are written out: left to the compiler, two variants of a loop
+// may fuse different products and differ in the last bit.
 __device__ inline float rcp_f(float x) { return __builtin_amdgcn_rcpf(x); }
 __device__ inline float sigmoid_f(float z) { return rcp_f(1.0f + __expf(-z)); }
 __device__ inline float tanh_f(float z) {
@@ -122,8 +124,8 @@ __device__ inline float tanh_f(float z) {
 __device__ inline void gru_cell(f32x4_t z, float& h) {
     const float rg = sigmoid_f(z[0]);
     const float ug = sigmoid_f(z[1]);
-    const float ng = tanh_f(z[3] + rg * z[2]);
-    h = (1.0f - ug) * ng + ug * h;
+    const float ng = tanh_f(fmaf(rg, z[2], z[3]));
+    h = fmaf(ug, h, (1.0f - ug) * ng);
 }
 
 // The tanh RNN cell in the four columns of a unit: the weights are packed so
@@ -136,7 +138,7 @@ __device__ inline void lstm_cell(f32x4_t z, float& c, float& h) {
     const float fg = sigmoid_f(z[1]);
     const float gg = tanh_f(z[2]);
     const float og = sigmoid_f(z[3]);
-    c = fg * c + ig * gg;
+    c = fmaf(fg, c, ig * gg);
     h = og * tanh_f(c);
 }
 

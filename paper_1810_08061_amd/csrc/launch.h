@@ -18,9 +18,11 @@ struct Workspace {
     float* gx;          // [B * T_max][4H] x W + b for valid (b, t), gate-interleaved columns
     void* hx;           // [4][bpad][hpad] recurrent operand (dtype), slot order; row-major in two
                         // buffers for the per-step path, MFMA fragment order in four for the persistent loop
-    unsigned* bar;      // grid-barrier counters: [0] global, [64 * (1 + x)] group x (zeroed by prep)
+    unsigned* bar;      // grid-barrier counters: [0] global, [64 * (1 + x)] group x, and a word of flags
+                        // after each (zeroed by prep)
     float* z;           // [bpad][4H] per-step pre-activations (per-step mode only)
     void* wt;           // bf16: W transposed to [np][dp] (gate-interleaved rows, zero padded)
+    void* ux;           // U in A-fragment blocks for the XCD-grouped loop, or null
     int32_t* stopped;   // [B] per-step path, termination from the state: 1 once row b ended
     int32_t* running;   // [T_max] per-step path: rows still running after step t
 };
@@ -43,12 +45,21 @@ hipError_t launch_cell_pack(const Dims& d, const void* W, const void* U, const f
 
 // Preparation: clamp and validate lengths, stable descending length sort,
 // per-step active counts and compact row offsets, compact row sources.
-hipError_t launch_prep(const Dims& d, const int32_t* lengths, const Workspace& ws, hipStream_t s);
+// stop: rows may end before their lengths, so the steps that some row ran
+// (meta->iters) start at zero for the loop to count.
+// With U and ws.ux, further workgroups of the launch write U for the
+// XCD-grouped loop: 1 KB blocks, block (ug, kb) the MFMA A-fragment of units
+// 4 ug .. 4 ug + 3 (16 gate-interleaved columns) and one run of k (32 in fp16,
+// 16 in fp32), zero past H; xc gives the padded sizes.
+struct XLoopConfig;
+hipError_t launch_prep(const Dims& d, const int32_t* lengths, const Workspace& ws, hipStream_t s,
+                       bool stop = false, const void* U = nullptr, const XLoopConfig* xc = nullptr);
 
 // The workspace of a persistent-mode LSTM forward carved from caller memory
 // (api.hip): returns its bytes; fills ws when base is not null.
+// ux_bytes: room for the packed U, or 0 for none.
 long long carve_forward_workspace(const Dims& d, char* base, Workspace* ws, long long* hx_off,
-                                  long long* hx_bytes);
+                                  long long* hx_bytes, long long ux_bytes);
 
 // Input projection over all valid (b, t): gx[r][c'] = x[rowsrc[r]] . W[:, col(c')] + b[col(c')].
 hipError_t launch_inproj(const Dims& d, const void* x, const void* W, const float* b,
@@ -93,6 +104,30 @@ int persistent_blocks_per_cu(int bf16, int mt, int ksw, int kw, int nst, int lds
 // Compiled variant with exactly (mt, kw, ksw) and the smallest state capacity >= nstate.
 bool persistent_pick_variant(int bf16, int mt, int kw, int ksw, int nstate, int* nst);
 int persistent_lds_bytes(int bf16, int mt, int kw, int nst, int hpad);
+
+// The loop in one group of workgroups per XCD (xloop.hip), where all of U fits
+// the CUs of one XCD and the batch its row tiles.
+struct XLoopConfig {
+    const void* variant;  // the compiled variant, or null: the device-wide loop
+    int ng_shift;         // 1 << ng_shift groups; rows are dealt to them by slot
+    int gsize;            // workgroups per group
+    int rg;               // rows per group, at most
+    int hpad, ugroups;    // the packed U: padded K, groups of four units; its bytes
+    long long ux_bytes;
+};
+// Whether the sizes take the grouped loop on a device of num_cus CUs; fills xc.
+bool xloop_pick(const Dims& d, int num_cus, XLoopConfig* xc);
+// Whether its grid is resident at once (mode: LoopMode).
+bool xloop_fits(const Dims& d, const XLoopConfig& xc, int mode, int num_cus);
+hipError_t launch_xloop(const Dims& d, const XLoopConfig& xc, const PersistentConfig& pc, const void* U,
+                        const float* h0, const float* c0, float* out_h, float* out_c,
+                        const Workspace& ws, hipStream_t s);
+
+// xloop_pick and xloop_fits; and either loop's launch, by xc.variant.
+bool xloop_for(const Dims& d, int mode, int num_cus, XLoopConfig* xc);
+hipError_t launch_loop(const Dims& d, const XLoopConfig& xc, const PersistentConfig& pc, const void* U,
+                       const float* h0, const float* c0, float* out_h, float* out_c,
+                       const Workspace& ws, hipStream_t s);
 
 // Whole forward in one single-workgroup launch (H <= 32).
 bool small_pick(int bf16, int B, int D, int H, int* kd, int* nt);

@@ -109,9 +109,14 @@ extern "C" int lstm_dyn_forward_noalloc(int B, int D, int H, int T, int dtype, c
     const Dims d{B, D, H, T, bf16, plan.hpad, plan.bpad, CELL_LSTM};
     Workspace ws;
     long long hx_off = 0, hx_bytes = 0;
-    const long long need = carve_forward_workspace(d, nullptr, &ws, &hx_off, &hx_bytes);
+    // the packed U is left out where it would not fit beside the rest
+    XLoopConfig xc{};
+    long long ux_bytes = !plan.single && xloop_for(d, 0, ds.num_cus, &xc) ? xc.ux_bytes : 0;
+    if (carve_forward_workspace(d, nullptr, &ws, &hx_off, &hx_bytes, ux_bytes) > LSTM_DYN_NOALLOC_SCRATCH_BYTES)
+        ux_bytes = 0;
+    const long long need = carve_forward_workspace(d, nullptr, &ws, &hx_off, &hx_bytes, ux_bytes);
     if (need > LSTM_DYN_NOALLOC_SCRATCH_BYTES) return LSTM_DYN_ERR_TOO_LARGE;
-    (void)carve_forward_workspace(d, ds.ptr, &ws, &hx_off, &hx_bytes);
+    (void)carve_forward_workspace(d, ds.ptr, &ws, &hx_off, &hx_bytes, ux_bytes);
     hipStream_t s = static_cast<hipStream_t>(stream);
     const unsigned long long timeout_ticks = (unsigned long long)(5.0 * 1e3 * (double)ds.wclk_khz);
 #define NA_CHECK(call)               \
@@ -125,17 +130,20 @@ extern "C" int lstm_dyn_forward_noalloc(int B, int D, int H, int T, int dtype, c
         NA_CHECK(launch_small(d, plan.single_kd, plan.single_nt, x, lengths, W, U, b, h0, c0, out_h,
                               out_c, nullptr, nullptr, ws, s));
     } else {
-        const int per_cu = persistent_blocks_per_cu(bf16, plan.mt, plan.ksw, plan.kw, plan.nstate,
-                                                    plan.lds_bytes, CELL_LSTM, 0);
-        if (per_cu < 1 || plan.groups > per_cu * ds.num_cus) return LSTM_DYN_ERR_UNSUPPORTED;
-        // the operand buffer holds the previous call's values in another layout
-        const long n16 = (long)(hx_bytes / 16);
-        long zgrid = (n16 + 255) / 256;
-        if (zgrid > 4L * ds.num_cus) zgrid = 4L * ds.num_cus;
-        hipLaunchKernelGGL(zero_kernel, dim3((unsigned)zgrid), dim3(256), 0, s,
-                           reinterpret_cast<uint4*>(ds.ptr + hx_off), n16);
-        NA_CHECK(hipGetLastError());
-        NA_CHECK(launch_prep(d, lengths, ws, s));
+        if (!xc.variant) {
+            const int per_cu = persistent_blocks_per_cu(bf16, plan.mt, plan.ksw, plan.kw, plan.nstate,
+                                                        plan.lds_bytes, CELL_LSTM, 0);
+            if (per_cu < 1 || plan.groups > per_cu * ds.num_cus) return LSTM_DYN_ERR_UNSUPPORTED;
+            // the operand buffer holds the previous call's values in another layout
+            // (the XCD-grouped loop writes its padding itself)
+            const long n16 = (long)(hx_bytes / 16);
+            long zgrid = (n16 + 255) / 256;
+            if (zgrid > 4L * ds.num_cus) zgrid = 4L * ds.num_cus;
+            hipLaunchKernelGGL(zero_kernel, dim3((unsigned)zgrid), dim3(256), 0, s,
+                               reinterpret_cast<uint4*>(ds.ptr + hx_off), n16);
+            NA_CHECK(hipGetLastError());
+        }
+        NA_CHECK(launch_prep(d, lengths, ws, s, false, U, &xc));
         if (bf16) {
             NA_CHECK(inproj_bf16_setup());
             const long long tiles = inproj_bf16_tiles_max(d);
@@ -147,7 +155,7 @@ extern "C" int lstm_dyn_forward_noalloc(int B, int D, int H, int T, int dtype, c
         }
         PersistentConfig pc{plan.mt, plan.groups, plan.ksw, plan.kw, plan.nstate, plan.lds_bytes,
                             timeout_ticks, nullptr, nullptr, nullptr};
-        NA_CHECK(launch_persistent(d, pc, U, h0, c0, out_h, out_c, ws, s));
+        NA_CHECK(launch_loop(d, xc, pc, U, h0, c0, out_h, out_c, ws, s));
     }
     if (status) {
         hipLaunchKernelGGL(status_kernel, dim3(1), dim3(1), 0, s, ws.meta, status);

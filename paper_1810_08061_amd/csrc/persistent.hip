@@ -32,13 +32,12 @@
 // holds the marker and uses later tiles as loaded; a marker that slipped into
 // an active row shows up as a NaN pre-activation, and the chunk is then redone
 // with every tile polled.  Every wait is bounded (then ERR_TIMEOUT).
-#include "launch.h"
+#include "loop.h"
 
 namespace ldyn {
 
 constexpr int P_LDS_KB = 144;           // dynamic LDS for partial sums and the Gx prefetch
 constexpr int P_MAX_ROWS = 512;         // batch rows the variants hold (8 owned row tiles per wave)
-constexpr int P_SC1 = 16;               // buffer-instruction cache policy: device scope
 
 struct PersistParams {
     const void* U;
@@ -70,9 +69,6 @@ struct PersistParams {
     float* save_c;
 };
 
-// What a variant of the loop does besides the plain forward.
-enum LoopMode { LM_PLAIN = 0, LM_STOP = 1, LM_SAVE = 2 };
-
 // Logical workgroup index: consecutive workgroups are dispatched to different
 // XCDs (round robin over 8); give the workgroups of one XCD adjacent unit
 // ranges so the columns of U and Gx they read share L2 lines.
@@ -80,13 +76,6 @@ __device__ inline int logical_group(int bid, int groups) {
     if ((groups & 7) != 0) return bid;
     return (bid & 7) * (groups >> 3) + (bid >> 3);
 }
-
-__device__ inline void drain_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
-// Data written before this kernel started and only read by it, seen through
-// the constant address space: wave-uniform reads of it become scalar loads,
-// which do not queue behind the vector loads in flight.
-typedef const __attribute__((address_space(4))) int32_t const_i32;
 
 // Barrier k (k = 0, 1, ...), split in two so work can be issued between the
 // arrival and the wait.  Arrival happens only after every wave of the
@@ -127,78 +116,6 @@ __device__ inline bool grid_wait(const PersistParams& p, int k, int* lds_ok) {
     }
     __syncthreads();
     return *lds_ok;
-}
-
-// Device-scope loads/stores of the operand buffer through a buffer resource.
-// An operand slot whose value for the coming step has not arrived yet holds
-// the all-ones pattern (a NaN).  operand() never produces it: a NaN h that
-// would convert to it is stored as the canonical quiet NaN instead.
-template <typename E> struct HxIO;
-// 16-bit operands (bf16 or fp16): T the element, V eight of them, QNAN the
-// canonical quiet NaN's bits.
-template <typename T, typename V, unsigned short QNAN> struct HxIO16 {
-    __device__ static inline V load(__amdgpu_buffer_rsrc_t R, unsigned byte_off) {
-        typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-        const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(R, byte_off, 0, P_SC1);
-        return __builtin_bit_cast(V, v);
-    }
-    __device__ static inline T operand(float h) {
-        const unsigned short b = __builtin_bit_cast(unsigned short, (T)h);
-        return __builtin_bit_cast(T, b == 0xffffu ? QNAN : b);
-    }
-    __device__ static inline void store(__amdgpu_buffer_rsrc_t R, unsigned byte_off, float h) {
-        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, operand(h)), R, byte_off, 0,
-                                              P_SC1);
-    }
-    // true if any of the KSW fragments holds the marker in one of its elements
-    template <int KSW>
-    __device__ static inline bool has_marker(const V* f) {
-        typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-        typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-        u16x2 m = {0, 0};
-#pragma unroll
-        for (int ks = 0; ks < KSW; ++ks) {
-            const u32x4 v = __builtin_bit_cast(u32x4, f[ks]);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const unsigned d = v[j];  // (a bit_cast of the subscript itself reads element 0)
-                m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, d));
-            }
-        }
-        return m[0] == 0xffffu || m[1] == 0xffffu;
-    }
-};
-template <> struct HxIO<EltH16> : HxIO16<_Float16, f16x8_t, 0x7e00> {};
-
-template <> struct HxIO<EltF32> {
-    __device__ static inline float load(__amdgpu_buffer_rsrc_t R, unsigned byte_off) {
-        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(R, byte_off, 0, P_SC1));
-    }
-    __device__ static inline float operand(float h) {
-        const unsigned b = __float_as_uint(h);
-        return __uint_as_float(b == 0xffffffffu ? 0x7fc00000u : b);
-    }
-    __device__ static inline void store(__amdgpu_buffer_rsrc_t R, unsigned byte_off, float h) {
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(operand(h)), R, byte_off, 0, P_SC1);
-    }
-    template <int KSW>
-    __device__ static inline bool has_marker(const float* f) {
-        unsigned m = 0;
-#pragma unroll
-        for (int ks = 0; ks < KSW; ++ks) m = max(m, __float_as_uint(f[ks]));
-        return m == 0xffffffffu;
-    }
-};
-
-// K index (relative to the wave's K range) of the first value lane l holds for
-// MFMA K-step ks.  bf16: 8 consecutive k per lane per step.  fp32 with at
-// least four steps: each lane holds 4 consecutive k for a group of four
-// steps (one 16-byte load feeds four MFMAs); the A- and B-fragments use the
-// same assignment, so the sum over k is unchanged.
-template <typename E, int KSW>
-__device__ inline int kslot(int ks, int l) {
-    if constexpr (E::KPL == 1 && KSW >= 4) return 16 * (ks >> 2) + 4 * (l >> 4) + (ks & 3);
-    else return ks * E::KSTEP + (l >> 4) * E::KPL;
 }
 
 // The operand buffer holds h in MFMA fragment order rather than row-major:

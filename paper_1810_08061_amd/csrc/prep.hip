@@ -13,12 +13,71 @@ constexpr int PREP_THREADS = 1024;
 constexpr int PREP_MAX_B = 8192;  // two int32 tables of B entries in LDS
 constexpr int PREP_REG_SLOTS = 256;  // slots whose batch rows each wave keeps in registers
 
+// U [H][4H] -> A-fragment blocks (launch.h), 64 k by 16 units at a time: a
+// thread reads four units of one gate at one k, the tile turns through LDS
+// as [gate-interleaved column][k], and 16-byte pieces leave it in block order.
+// The loop's workgroups each read their part of U once per forward; taken
+// straight from U, by 8-byte pieces 8 H bytes apart, that took 27 us of the loop
+// launch at H = 256 (fp32) and 100 us at H = 1024 (bf16), in every XCD anew.
+// Packed here it runs beside the length sort, which keeps one CU busy.
+struct PackUParams {
+    const void* U;
+    void* ux;
+    int H, hpad, ugroups, bf16;
+};
+
+template <typename E>
+__device__ inline void pack_u_tiles(const PackUParams& q, void* lds) {
+    using S = typename E::store_t;
+    using Src = typename E::src_t;
+    typedef Src src4_t __attribute__((ext_vector_type(4)));
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int CK = 16 / (int)sizeof(S), KB = 4 * CK, LDT = 64 + CK;
+    S* const tile = static_cast<S*>(lds);  // [64 columns][LDT]
+    const Src* U = static_cast<const Src*>(q.U);
+    const int H = q.H, tid = threadIdx.x, nkt = q.hpad / 64, nut = (q.ugroups + 3) / 4;
+    const size_t H4 = 4 * (size_t)H;
+    for (int it = blockIdx.x - 1; it < nkt * nut; it += gridDim.x - 1) {
+        const int k0 = it % nkt * 64, u0 = it / nkt * 16;
+        {
+            const int quad = tid & 3, gate = (tid >> 2) & 3, kl = tid >> 4;
+            const int k = k0 + kl, u = u0 + 4 * quad;
+            src4_t v = src4_t{(Src)0.0f, (Src)0.0f, (Src)0.0f, (Src)0.0f};
+            if ((H & 3) == 0) {  // (U is 16-byte aligned)
+                if (k < H && u < H) v = *reinterpret_cast<const src4_t*>(U + (size_t)k * H4 + (size_t)gate * H + u);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (k < H && u + e < H) v[e] = U[(size_t)k * H4 + (size_t)gate * H + u + e];
+            }
+            __syncthreads();  // the last tile has been read
+#pragma unroll
+            for (int e = 0; e < 4; ++e) tile[(4 * (4 * quad + e) + gate) * LDT + kl] = E::from_src(v[e]);
+        }
+        __syncthreads();
+        constexpr int KBT = 64 / KB;  // blocks along k in the tile
+        if (tid < 4 * KBT * 64) {
+            const int lane = tid & 63, kb = (tid >> 6) % KBT, ug = (tid >> 6) / KBT;
+            if (u0 / 4 + ug < q.ugroups)
+                static_cast<u32x4*>(q.ux)[((size_t)(u0 / 4 + ug) * (q.hpad / KB) + k0 / KB + kb) * 64 + lane] =
+                    *reinterpret_cast<const u32x4*>(tile + (ug * 16 + (lane & 15)) * LDT + kb * KB + (lane >> 4) * CK);
+        }
+    }
+}
+constexpr int PACK_LDS = 64 * (64 + 4) * 4 > 64 * (64 + 8) * 2 ? 64 * (64 + 4) * 4 : 64 * (64 + 8) * 2;
+
 __global__ void __launch_bounds__(PREP_THREADS)
 prep_kernel(const int32_t* __restrict__ lengths, int B, int T, Meta* __restrict__ meta,
             int32_t* __restrict__ perm, int32_t* __restrict__ offsets,
-            int32_t* __restrict__ rowsrc, unsigned* __restrict__ bar) {
+            int32_t* __restrict__ rowsrc, unsigned* __restrict__ bar, int iters0,
+            PackUParams pack) {
     constexpr int NW = PREP_THREADS / 64;
-    extern __shared__ int32_t sh[];
+    extern __shared__ __attribute__((aligned(16))) int32_t sh[];
+    if (blockIdx.x > 0) {
+        if (pack.bf16) pack_u_tiles<EltH16>(pack, sh);
+        else pack_u_tiles<EltF32>(pack, sh);
+        return;
+    }
     int32_t* len = sh;       // [B] clamped lengths: batch order, then slot order
     int32_t* sperm = sh + B; // [B] slot -> batch index
     __shared__ int bad, maxlen, wsum[NW];
@@ -27,7 +86,10 @@ prep_kernel(const int32_t* __restrict__ lengths, int B, int T, Meta* __restrict_
         bad = 0;
         maxlen = 0;
     }
-    if (tid < BAR_WORDS / 64) bar[64 * tid] = 0u;  // grid-barrier counters of the loop kernel
+    if (tid < BAR_WORDS / 64) {  // grid-barrier counters and flags of the loop kernel
+        bar[64 * tid] = 0u;
+        bar[64 * tid + 1] = 0u;
+    }
     __syncthreads();
     int mx = 0, bd = 0;
     for (int i = tid; i < B; i += PREP_THREADS) {
@@ -162,15 +224,24 @@ prep_kernel(const int32_t* __restrict__ lengths, int B, int T, Meta* __restrict_
     if (tid == 0) {
         meta->max_len = ml;
         meta->status = bad ? STATUS_BAD_LENGTHS : 0;
-        meta->iters = ml;
+        meta->iters = iters0 < 0 ? ml : iters0;
     }
 }
 
-hipError_t launch_prep(const Dims& d, const int32_t* lengths, const Workspace& ws, hipStream_t s) {
+hipError_t launch_prep(const Dims& d, const int32_t* lengths, const Workspace& ws, hipStream_t s,
+                       bool stop, const void* U, const XLoopConfig* xc) {
     if (d.B > PREP_MAX_B) return hipErrorInvalidValue;
-    const size_t lds = (size_t)2 * d.B * sizeof(int32_t);
-    hipLaunchKernelGGL(prep_kernel, dim3(1), dim3(PREP_THREADS), lds, s, lengths, d.B, d.T, ws.meta,
-                       ws.perm, ws.offsets, ws.rowsrc, ws.bar);
+    size_t lds = (size_t)2 * d.B * sizeof(int32_t);
+    PackUParams pack{};
+    int grid = 1;
+    if (U && xc && xc->variant && ws.ux) {
+        pack = PackUParams{U, ws.ux, d.H, xc->hpad, xc->ugroups, d.bf16};
+        const int tiles = (xc->hpad / 64) * ((xc->ugroups + 3) / 4);
+        grid += tiles < 255 ? tiles : 255;
+        if (lds < PACK_LDS) lds = PACK_LDS;
+    }
+    hipLaunchKernelGGL(prep_kernel, dim3(grid), dim3(PREP_THREADS), lds, s, lengths, d.B, d.T, ws.meta,
+                       ws.perm, ws.offsets, ws.rowsrc, ws.bar, stop ? 0 : -1, pack);
     return hipGetLastError();
 }
 
