@@ -261,11 +261,15 @@ int lstm_dyn_forward_train(lstm_dyn_t* h, const void* x, const int32_t* lengths,
  * kept pre-activations; dh <- dz U^T and the weight gradients (sums over all
  * valid steps) are products with fp32 accumulation, of fp32 operands with
  * fp32 data and of fp16 operands with bf16 data (each scaled by a power of
- * two: U and the weight-gradient operands as a whole, dz per row or per row
- * and 32-column block).  Synchronises once with the host (the step offsets),
- * then issues two launches per step; a persistent handle with bf16 data (H
- * even, 16 <= H <= 2048, B <= 512) takes the steps with at most 16 rows in
- * one cooperative launch with a bounded grid barrier per step (a timeout
+ * two: U per row or as a whole, the weight-gradient operands as a whole, dz
+ * per row or per row and 32-column block).  Waits once or twice for copies to
+ * the host (the sum of lengths, the operands' largest magnitudes).  The reverse
+ * loop of a persistent handle is one cooperative launch where U fits the CUs of
+ * one XCD (B <= 256 on a 256-CU device; bf16 data: H < 1024, fp32 data: H <=
+ * 512) and, with bf16 data, where H is a multiple of 256 (H <= 2048, B <=
+ * 512); else two launches per step, with bf16 data (H even, 16 <= H <= 2048,
+ * B <= 512) but for the steps with at most 16 rows, which are one
+ * cooperative launch.  Every wait of those launches is bounded (a timeout
  * shows in LSTM_DYN_Q_LAST_STATUS).  Consumes what the forward kept (a
  * second backward needs another forward for training).  Returns LSTM_DYN_OK,
  * ERR_INVALID (bad arguments, or no forward for training kept), ERR_HIP.

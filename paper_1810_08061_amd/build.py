@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "liblstm_dyn.so")
 LIB_STRESS = os.path.join(HERE, "liblstm_dyn_stress.so")
-SOURCES = ["api.hip", "prep.hip", "gemm.hip", "persistent.hip", "xloop_h16.hip", "xloop_h16w.hip", "xloop_f32.hip", "xloop.hip", "step.hip", "small.hip", "inproj.hip", "seq.hip", "pack.hip", "bwd.hip", "bwdblk.hip", "noalloc.hip"]
+SOURCES = ["api.hip", "prep.hip", "gemm.hip", "persistent.hip", "xloop_h16.hip", "xloop_h16w.hip", "xloop_f32.hip", "xloop.hip", "xbwd_h16.hip", "xbwd_f32.hip", "xbwd.hip", "step.hip", "small.hip", "inproj.hip", "seq.hip", "pack.hip", "bwd.hip", "bwdblk.hip", "noalloc.hip"]
 ARCH = "gfx950"
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HIPCC = os.environ.get("HIPCC", f"{ROCM}/bin/hipcc")

@@ -82,6 +82,10 @@ struct TrainWs {
     // the reverse loop in one launch (bf16 data, persistent handles that fit):
     // all steps with column blocks of U (bwdblk.hip), else the steps with few
     // rows (bwd.hip) and two launches for each other step
+    ldyn::XBwdConfig xb;    // the XCD-grouped reverse loop (xbwd.hip), or variant null
+    void* xux;              // its packed U, and the inverse scales of U's rows
+    float* xus;
+    hipEvent_t copied;      // the host copies of the step offsets have arrived
     int block_groups;       // workgroups of the whole-loop launch, or 0
     int loop_groups;        // workgroups of the few-row launch, or 0
     _Float16* dzx;          // [2][bpad][kp] each step's published dz
@@ -552,6 +556,7 @@ extern "C" int lstm_dyn_destroy(lstm_dyn_t* h) {
         if (h->train->rb && g_rb.destroy_handle(h->train->rb) != rocblas_status_success)
             rc = LSTM_DYN_ERR_HIP;
         if (h->train->block && hipFree(h->train->block) != hipSuccess) rc = LSTM_DYN_ERR_HIP;
+        if (h->train->copied && hipEventDestroy(h->train->copied) != hipSuccess) rc = LSTM_DYN_ERR_HIP;
         if (h->train->host_offsets && hipHostFree(h->train->host_offsets) != hipSuccess)
             rc = LSTM_DYN_ERR_HIP;
         delete h->train;
@@ -801,8 +806,10 @@ static int ensure_train(lstm_dyn* h) {
                     ou16 = take(h16 ? 2 * H * 4 * H : 0), odzs = take(h16 ? 2 * B * 4 * H : 0),
                     osr = take(4 * B), osm = take(256), ocs = take(4LL * BWD_CS_CHUNKS * 4 * H);
     const bool pers16 = h16 && h->mode == LSTM_DYN_PERSISTENT;
-    tw->block_groups = pers16 ? bwd_block_fits(h->dims, h->num_cus) : 0;
-    tw->loop_groups = pers16 && !tw->block_groups ? bwd_loop_fits(h->dims, h->num_cus) : 0;
+    if (h->mode == LSTM_DYN_PERSISTENT) (void)xbwd_pick(h->dims, h->num_cus, &tw->xb);
+    const bool xb = tw->xb.variant != nullptr;
+    tw->block_groups = pers16 && !xb ? bwd_block_fits(h->dims, h->num_cus) : 0;
+    tw->loop_groups = pers16 && !xb && !tw->block_groups ? bwd_loop_fits(h->dims, h->num_cus) : 0;
     int kp = 0, nblk = 0;
     if (tw->loop_groups) bwd_loop_shape((int)H, &kp, &nblk);
     int slots = 2;  // the few-row launch: by step parity
@@ -812,11 +819,12 @@ static int ensure_train(lstm_dyn* h) {
         slots = 4;
     }
     const bool one_launch = tw->block_groups || tw->loop_groups;
-    tw->dzx_bytes = 2LL * slots * bpad * kp;
-    tw->dzs_bytes = 4LL * slots * bpad * nblk;
+    tw->dzx_bytes = xb ? tw->xb.dzx_bytes : 2LL * slots * bpad * kp;
+    tw->dzs_bytes = xb ? tw->xb.dzs_bytes : 4LL * slots * bpad * nblk;
     tw->pdh_bytes = tw->block_groups ? 4LL * 4 * 4 * bpad * H : 0;
     const long long odzx = take(tw->dzx_bytes), odzsc = take(tw->dzs_bytes), opdh = take(tw->pdh_bytes),
-                    obar = take(tw->loop_groups ? 9 * 64 * 4 : 0);
+                    obar = take(tw->loop_groups || xb ? 9 * 64 * 4 : 0), oxux = take(tw->xb.ux_bytes),
+                    oxus = take(xb ? 4 * H : 0);
     if (hipMalloc(&tw->block, (size_t)o) != hipSuccess) {
         (void)hipGetLastError();
         delete tw;
@@ -843,13 +851,21 @@ static int ensure_train(lstm_dyn* h) {
     tw->dzs16 = h16 ? reinterpret_cast<_Float16*>(base + odzs) : nullptr;
     tw->srow = reinterpret_cast<float*>(base + osr);
     tw->amax = reinterpret_cast<unsigned*>(base + osm);
-    tw->dzx = one_launch ? reinterpret_cast<_Float16*>(base + odzx) : nullptr;
-    tw->dzs = one_launch ? reinterpret_cast<float*>(base + odzsc) : nullptr;
+    tw->dzx = one_launch || xb ? reinterpret_cast<_Float16*>(base + odzx) : nullptr;
+    tw->dzs = one_launch || xb ? reinterpret_cast<float*>(base + odzsc) : nullptr;
+    tw->xux = xb ? base + oxux : nullptr;
+    tw->xus = xb ? reinterpret_cast<float*>(base + oxus) : nullptr;
     tw->pdh = tw->block_groups ? reinterpret_cast<float*>(base + opdh) : nullptr;
-    tw->bar = tw->loop_groups ? reinterpret_cast<unsigned*>(base + obar) : nullptr;
+    tw->bar = tw->loop_groups || xb ? reinterpret_cast<unsigned*>(base + obar) : nullptr;
     if (hipHostMalloc(reinterpret_cast<void**>(&tw->host_offsets), (size_t)(T + 8) * sizeof(int32_t),
                       hipHostMallocDefault) != hipSuccess) {
         (void)hipFree(tw->block);
+        delete tw;
+        return LSTM_DYN_ERR_HIP;
+    }
+    if (hipEventCreateWithFlags(&tw->copied, hipEventDisableTiming) != hipSuccess) {
+        (void)hipFree(tw->block);
+        (void)hipHostFree(tw->host_offsets);
         delete tw;
         return LSTM_DYN_ERR_HIP;
     }
@@ -859,6 +875,7 @@ static int ensure_train(lstm_dyn* h) {
         g_rb.set_atomics_mode(tw->rb, rocblas_atomics_not_allowed) != rocblas_status_success) {
         (void)hipFree(tw->block);
         (void)hipHostFree(tw->host_offsets);
+        (void)hipEventDestroy(tw->copied);
         delete tw;
         return LSTM_DYN_ERR_HIP;
     }
@@ -1037,29 +1054,53 @@ extern "C" int lstm_dyn_backward(lstm_dyn_t* h, const void* x, const int32_t* le
     } while (0)
     RB_CHECK(g_rb.set_stream(tw->rb, s));
     LD_CHECK(launch_bwd_weights(d, W, d.D, tw->w_il, s));
-    LD_CHECK(launch_bwd_weights(d, U, d.H, tw->u_il, s));
-    h->launches_last += 2;
-    if (d.bf16) {  // the largest |U|, for U's fp16 scale
-        LD_CHECK(hipMemsetAsync(tw->amax, 0, 5 * sizeof(unsigned), s));
-        LD_CHECK(launch_bwd_absmax(tw->u_il, (long)d.H * H4, tw->amax + 4, s));
-        LD_CHECK(hipMemcpyAsync(tw->host_offsets + d.T + 2, tw->amax + 4, sizeof(unsigned),
-                                hipMemcpyDeviceToHost, s));
+    h->launches_last++;
+    const bool xb = tw->xb.variant != nullptr;
+    if (xb) {
+        // U for the XCD-grouped reverse loop (and its counters and maxima cleared)
+        LD_CHECK(launch_xbwd_pack(d, tw->xb, U, tw->xux, tw->xus, tw->bar, tw->amax, s));
         h->launches_last++;
+    } else {
+        LD_CHECK(launch_bwd_weights(d, U, d.H, tw->u_il, s));
+        h->launches_last++;
+        if (d.bf16) {  // the largest |U|, for U's fp16 scale
+            LD_CHECK(hipMemsetAsync(tw->amax, 0, 5 * sizeof(unsigned), s));
+            LD_CHECK(launch_bwd_absmax(tw->u_il, (long)d.H * H4, tw->amax + 4, s));
+            LD_CHECK(hipMemcpyAsync(tw->host_offsets + d.T + 2, tw->amax + 4, sizeof(unsigned),
+                                    hipMemcpyDeviceToHost, s));
+            h->launches_last++;
+        }
+        LD_CHECK(hipMemcpyAsync(tw->host_offsets, h->ws.offsets, (size_t)(d.T + 1) * sizeof(int32_t),
+                                hipMemcpyDeviceToHost, s));
     }
-    // step offsets and the sum of lengths of the forward, on the host
-    LD_CHECK(hipMemcpyAsync(tw->host_offsets, h->ws.offsets, (size_t)(d.T + 1) * sizeof(int32_t),
-                            hipMemcpyDeviceToHost, s));
+    // step offsets (where the host issues the steps) and the sum of lengths of
+    // the forward, on the host
     LD_CHECK(hipMemcpyAsync(tw->host_offsets + d.T + 1, &h->ws.meta->total_rows, sizeof(int32_t),
                             hipMemcpyDeviceToHost, s));
     LD_CHECK(hipMemcpyAsync(h->host_maxlen, &h->ws.meta->max_len, sizeof(int32_t),
                             hipMemcpyDeviceToHost, s));
-    LD_CHECK(hipStreamSynchronize(s));
+    if (xb) {
+        // the loop needs nothing of the host: it runs while the host waits for
+        // the copies only
+        LD_CHECK(hipEventRecord(tw->copied, s));
+        LD_CHECK(launch_xbwd(d, tw->xb, tw->xux, d.bf16 ? tw->xus : nullptr, tw->save_h, tw->save_c, d_seq,
+                             d_out_h, d_out_c, dh0, dc0, tw->dzx, tw->dzs, tw->amax + 0, tw->bar,
+                             h->timeout_ticks, h->trace, h->ws, s));
+        h->launches_last++;
+        LD_CHECK(hipEventSynchronize(tw->copied));
+    } else {
+        LD_CHECK(hipStreamSynchronize(s));
+    }
     const int32_t* off = tw->host_offsets;
     const int rows = off[d.T + 1], max_len = *h->host_maxlen;
     const float one = 1.0f, zero = 0.0f;
-    LD_CHECK(launch_bwd_init(d, d_out_h, d_out_c, tw->dH, tw->dC, h->ws, s));
-    h->launches_last++;
-    if (!d.bf16) {
+    if (!xb) {
+        LD_CHECK(launch_bwd_init(d, d_out_h, d_out_c, tw->dH, tw->dC, h->ws, s));
+        h->launches_last++;
+    }
+    if (xb) {
+        // dh0 and dc0 are written
+    } else if (!d.bf16) {
         for (int t = max_len - 1; t >= 0; --t) {
             const int act = off[t + 1] - off[t];
             LD_CHECK(launch_bwd_cell(d, t, off[t], act, tw->save_h, tw->save_c, d_seq, tw->dH,
@@ -1071,6 +1112,7 @@ extern "C" int lstm_dyn_backward(lstm_dyn_t* h, const void* x, const int32_t* le
             h->launches_last += 2;
         }
         LD_CHECK(launch_bwd_state_out(d, tw->dH, tw->dC, nullptr, dh0, dc0, h->ws, s));
+        h->launches_last++;
     } else {
         // bf16 data: dh = dz U^T on fp16 operands, U scaled once, each row's dz
         // by its own power of two (kept in srow and divided out when dH is read)
@@ -1119,8 +1161,8 @@ extern "C" int lstm_dyn_backward(lstm_dyn_t* h, const void* x, const int32_t* le
             h->launches_last += 2;
         }
         LD_CHECK(launch_bwd_state_out(d, tw->dH, tw->dC, tw->srow, dh0, dc0, h->ws, s));
+        h->launches_last++;
     }
-    h->launches_last++;
     if (rows > 0) {
         // (bf16: the largest |x| of the rows for x's fp16 scale, in the same pass)
         LD_CHECK(launch_bwd_gather_x(d, x, rows, tw->xc, d.bf16 ? tw->amax + 1 : nullptr, h->ws, s));
@@ -1144,9 +1186,9 @@ extern "C" int lstm_dyn_backward(lstm_dyn_t* h, const void* x, const int32_t* le
             // alpha undoing the scales
             const long n_dz = (long)rows * H4, n_x = (long)rows * d.D, n_h = (long)rows * d.H,
                        n_w = (long)d.D * H4;
-            // (the whole-loop launch took the largest |dz| as it went, and the
+            // (the one-launch loops took the largest |dz| as they went, and the
             // gather of x its largest |x|)
-            if (!tw->block_groups) LD_CHECK(launch_bwd_absmax(h->ws.gx, n_dz, tw->amax + 0, s));
+            if (!tw->block_groups && !xb) LD_CHECK(launch_bwd_absmax(h->ws.gx, n_dz, tw->amax + 0, s));
             LD_CHECK(launch_bwd_absmax(tw->save_h, n_h, tw->amax + 2, s));
             LD_CHECK(launch_bwd_absmax(tw->w_il, n_w, tw->amax + 3, s));
             unsigned* am = reinterpret_cast<unsigned*>(tw->host_offsets + d.T + 3);
@@ -1173,7 +1215,7 @@ extern "C" int lstm_dyn_backward(lstm_dyn_t* h, const void* x, const int32_t* le
                                      rows, H4, &a_x, tw->w16, f16, H4, tw->dz16, f16, H4, &zero,
                                      tw->xc, f32, d.D, tw->xc, f32, d.D, f32,
                                      rocblas_gemm_algo_standard, 0, 0));
-            h->launches_last += tw->block_groups ? 10 : 11;
+            h->launches_last += tw->block_groups || xb ? 10 : 11;
         }
     } else {
         LD_CHECK(hipMemsetAsync(tw->dw_il, 0, (size_t)d.D * H4 * sizeof(float), s));

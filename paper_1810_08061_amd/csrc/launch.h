@@ -203,6 +203,26 @@ hipError_t launch_bwd_block(const Dims& d, const _Float16* u16, float alpha_u, c
                             const float* save_c, const float* dseq, float* dH, float* dC, _Float16* dzx,
                             float* dzs, float* pdh, unsigned* amax_dz, unsigned long long timeout_ticks,
                             unsigned long long* trace, const Workspace& ws, hipStream_t s);
+// The reverse loop in one group of workgroups per XCD (xbwd.hip), for persistent
+// handles where all of U fits the CUs of one XCD: one cooperative launch for
+// every step, dh0 and dc0 written to the caller's buffers.  xbwd_pick: false
+// where it does not apply.  launch_xbwd_pack fills ux (ux_bytes) and us [H]
+// (bf16 data) from U [H][4H] in gate blocks and clears bar and amax [5];
+// dzx and dzs need no contents.
+struct XBwdConfig {
+    const void* variant;  // the compiled variant, or null
+    int ng_shift, gsize, rg;  // as in XLoopConfig
+    int kpad, urows;          // padded 4H; rows of U that the groups hold
+    long long ux_bytes, dzx_bytes, dzs_bytes;
+};
+bool xbwd_pick(const Dims& d, int num_cus, XBwdConfig* xb);
+hipError_t launch_xbwd_pack(const Dims& d, const XBwdConfig& xb, const void* U, void* ux, float* us,
+                            unsigned* bar, unsigned* amax, hipStream_t s);
+hipError_t launch_xbwd(const Dims& d, const XBwdConfig& xb, const void* ux, const float* us,
+                       const float* save_h, const float* save_c, const float* dseq, const float* d_out_h,
+                       const float* d_out_c, float* dh0, float* dc0, void* dzx, void* dzs, unsigned* amax_dz,
+                       unsigned* bar, unsigned long long timeout_ticks, unsigned long long* trace,
+                       const Workspace& ws, hipStream_t s);
 // xc = the compact rows of x in fp32; amax (or null) receives the largest
 // |x| of them, as float bits, by atomic maximum.
 hipError_t launch_bwd_gather_x(const Dims& d, const void* x, long rows, float* xc, unsigned* amax,

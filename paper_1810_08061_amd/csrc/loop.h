@@ -102,4 +102,8 @@ __device__ inline int kslot(int ks, int l) {
     else return ks * E::KSTEP + (l >> 4) * E::KPL;
 }
 
+// Workgroup barrier after this wave's LDS accesses; loads and stores in flight
+// stay in flight.
+__device__ inline void x_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 }  // namespace ldyn

@@ -29,10 +29,14 @@ static xloop_fn xloop_of(const XLoopConfig& xc, int cell, int mode) {
 // and fp32 data up to H = 512 (the U of 32 workgroups is 128 registers of each
 // product wave there), 32 rows per group (two row tiles; more would have the
 // gate waves' state spill, and beyond 256 rows the device-wide loop's chunks
-// are full).  It was faster at every size measured within these; fp32 at H =
-// 512, where its MFMAs take longest (1.7 us a step and tile), included.
+// are full).  It was faster at every size measured within these but one: fp32
+// beyond H = 384 with a single row tile in all, where its MFMAs (1.7 us a step
+// and tile, U over 32 CUs) cost more than the exchange through memory saves
+// (whole forwards of 100 full steps at H = 512: 8 rows 336 against 302 us, 64
+// rows 374 against 527; H = 384, 3 rows: 242 against 312).
 bool xloop_pick(const Dims& d, int num_cus, XLoopConfig* xc) {
     *xc = XLoopConfig{};
+    if (!d.bf16 && d.H > 384 && d.B <= 16) return false;
     int shift = 3;
     while (shift >= 0 && (X_GROUP << shift) > num_cus) --shift;
     if (shift < 0) return false;

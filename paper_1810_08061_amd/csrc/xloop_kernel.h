@@ -105,10 +105,6 @@ struct XLayout {
     static_assert(TP >= 1 && 2 * PART <= ROOM, "LDS");
 };
 
-// Workgroup barrier after this wave's LDS accesses; loads and stores in flight
-// stay in flight.
-__device__ inline void x_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 template <typename E, int MT, int KSW, int KW, int NT, int CELL, int LMODE>
 __global__ void __launch_bounds__(X_WAVES * 64, 1)
 xloop_kernel(XLoopParams p) {
@@ -139,6 +135,7 @@ xloop_kernel(XLoopParams p) {
     const int g = blockIdx.x & (ng - 1), role = blockIdx.x >> p.ng_shift;
     const int B = p.B, H = p.H, H4 = 4 * H, RG = p.rg;
     if (g >= B) return;  // a group without rows
+    const unsigned long long t_begin = wall_clock64();  // the bound of the start barrier counts from here
     const int Bg = (B - g + ng - 1) >> p.ng_shift;  // rows of this group: slots g, g + ng, ...
     const int u0 = role * 4 * MT;
     const bool is_mma = w < KW;
@@ -331,9 +328,8 @@ xloop_kernel(XLoopParams p) {
                                                         __HIP_MEMORY_SCOPE_AGENT);
             asm volatile("s_waitcnt vmcnt(0)" ::"v"(seen) : "memory");  // the mask before the count
             __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const unsigned long long t0 = wall_clock64();
             while (__hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (unsigned)p.gsize) {
-                if (wall_clock64() - t0 > p.timeout_ticks) {
+                if (wall_clock64() - t_begin > p.timeout_ticks) {
                     ok = 0;
                     __hip_atomic_fetch_or(&p.meta->status, STATUS_TIMEOUT, __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_AGENT);
@@ -437,6 +433,7 @@ xloop_kernel(XLoopParams p) {
             const unsigned long long t0 = wall_clock64();
             int tries = 0;
             do {
+                __builtin_amdgcn_s_sleep(1);
                 load_all();
                 // (the clock costs more than a try: read at every fourth)
                 if ((++tries & 3) == 0 && wall_clock64() - t0 > p.timeout_ticks) {
@@ -600,6 +597,11 @@ xloop_kernel(XLoopParams p) {
         next_step(o4);
         return true;
     };
+    // The gate waves' memory instructions go before those of the (older) waves
+    // that poll, which would otherwise hold up the stores that are polled for.
+    if constexpr (!BOTH) {
+        if (!is_mma) __builtin_amdgcn_s_setprio(3);
+    }
     if (alive && max_len > 0) {
         if (!is_mma || BOTH) {
             if (o1 - o0 > g) load_gx(gxr[0], o0, o1 - o0);
