@@ -287,7 +287,10 @@ xbwd_kernel(XBwdParams p) {
     // Row tile j: the wave's part of dh_t into LDS; false where the loop ended
     // at the last barrier.
     auto product_tile = [&](int j, int rows) __attribute__((always_inline)) -> bool {
-        const int r = j * 16 + (l & 15), rr = r < rows ? r : 0;  // (no row: the group's first again)
+        // (lanes without a row take the tile's first: its products are not used,
+        // and no row of another tile may stand in, whose slot may be marked
+        // again while this tile is still read)
+        const int r = j * 16 + (l & 15), rr = r < rows ? r : j * 16;
         const unsigned slot = turn & 3u;
         const unsigned lane = slot * ring + (unsigned)kb0 * blk_bytes + (unsigned)((l >> 4) * RG + rr) * 16u;
         const unsigned slane = slot * sring + (unsigned)(rr * NBLK + kb0) * 2u;

@@ -407,11 +407,12 @@ xloop_kernel(XLoopParams p) {
     // at the last barrier (known only here, so that the loads travel while the
     // flags are read).
     auto fetch_tile = [&](int j, int rows) __attribute__((always_inline)) -> bool {
-        // lanes without an active row read the group's first row instead,
-        // whose products they then repeat
+        // lanes without an active row read the tile's first row instead, whose
+        // products they then repeat (no row of another tile may stand in, whose
+        // slot other workgroups may mark again while this tile is still read)
         const int r = j * 16 + (l & 15);
         const unsigned lane = (unsigned)(t & 3) * ring + (unsigned)(kw0 / KB) * blk_bytes +
-                              (unsigned)((l >> 4) * RG + (r < rows ? r : 0)) * 16u;
+                              (unsigned)((l >> 4) * RG + (r < rows ? r : j * 16)) * 16u;
         stress_delay(t, 1 + j);
         auto load_all = [&]() __attribute__((always_inline)) {
 #pragma unroll

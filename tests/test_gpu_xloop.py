@@ -70,3 +70,31 @@ def test_noalloc_with_and_without_room_for_packed_u(T):
     assert int(st[0]) == ld.OK
     assert torch.equal(h, oh) and torch.equal(c, oc)
     m.close()
+
+
+@pytest.mark.parametrize("dt,H,B", [("bf16", 512, 256), ("f32", 130, 200), ("bf16", 800, 256)])
+def test_rows_ending_in_later_tiles(dt, H, B):
+    """Rows end one by one while a group has two row tiles, forward and back: a
+    lane whose row has ended must not wait for a row of another tile, whose
+    slot other workgroups may already have marked for a later step."""
+    import torch
+    D, T = 16, 300
+    inp = workloads.random_case(6500 + H, B, D, H, T, dtype=dt)
+    inp.lengths[:] = np.maximum(T - np.arange(B), 1)
+    m = ld.LstmDyn(B, D, H, T, dt, "persistent")
+    m.set_option(ld.OPT_TIMEOUT_US, 200000)
+    dev = to_device(inp)
+    say(f"case xloop rows ending {dt} H={H} B={B}")
+    h, c = m.forward(*dev)
+    dh = torch.ones(B, H, device="cuda")
+    m.forward_train(*dev)
+    assert m.query(ld.Q_LAST_STATUS) == ld.OK
+    m.backward(*dev, dh, dh)
+    torch.cuda.synchronize()
+    assert m.query(ld.Q_LAST_STATUS) == ld.OK
+    rows = [0, 17, B // 2, B - 1]
+    sub = workloads.Inputs(x=inp.x[rows], lengths=inp.lengths[rows], W=inp.W, U=inp.U, b=inp.b, h0=inp.h0[rows],
+                           c0=inp.c0[rows], dtype=inp.dtype)
+    ho, co = oracle.forward_inputs(sub)
+    assert max_err(h.cpu().numpy()[rows], ho) <= TOL[dt] and max_err(c.cpu().numpy()[rows], co) <= TOL[dt]
+    m.close()
