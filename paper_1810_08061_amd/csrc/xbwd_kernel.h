@@ -523,9 +523,11 @@ xbwd_kernel(XBwdParams p) {
         }
     };
 
-    // One step; false where the loop ends.  PAR: parity of the steps done.
-    auto step = [&](auto par) __attribute__((always_inline)) -> bool {
+    // One step; false where the loop ends.  PAR: parity of the steps done; MMA:
+    // a product wave (see xloop_kernel.h).
+    auto step = [&](auto par, auto mma) __attribute__((always_inline)) -> bool {
         constexpr int PAR = decltype(par)::value;
+        constexpr bool MMA = decltype(mma)::value;
         if (t < -1) return false;
         // values derived from the lane number (addresses) are formed again in
         // each step rather than kept live across it
@@ -553,7 +555,7 @@ xbwd_kernel(XBwdParams p) {
                 if (j < tiles_p) ++cnt;
             }
             if (tr0) p.trace[4 * ti + 2] = wall_clock64();
-        } else if (is_mma) {
+        } else if constexpr (MMA) {
             for (int j = 0; j < tiles_p; ++j) {
                 if (!product_tile(j, rows_p)) return false;
                 x_barrier();
@@ -604,7 +606,12 @@ xbwd_kernel(XBwdParams p) {
     }
     using even_t = std::integral_constant<int, 0>;
     using odd_t = std::integral_constant<int, 1>;
-    while (step(even_t{}) && step(odd_t{})) {
+    if (is_mma) {
+        while (step(even_t{}, std::true_type{}) && step(odd_t{}, std::true_type{})) {
+        }
+    } else if constexpr (!BOTH) {
+        while (step(even_t{}, std::false_type{}) && step(odd_t{}, std::false_type{})) {
+        }
     }
     drain_stores();
     if (ci >= 0) {
