@@ -58,26 +58,25 @@ struct TrainWs {
     void* block;
     float* save_h;  // [B*T][H] the state each step started from, compact rows
     float* save_c;  // [B*T][H]
-    float* xc;      // [B*T][D] x in compact rows (fp32), then the rows of dx
-    float* w_il;    // [D][4H] W in fp32, gate-interleaved columns
-    float* u_il;    // [H][4H]
-    float* dw_il;   // [D][4H] weight gradients, gate-interleaved columns
-    float* du_il;   // [H][4H]
-    float* db_il;   // [4H]
+    float* xc;      // [B*T][D] the compact rows of dx (behind save_c)
+    float* xh;      // fp32: [B*T][D + H] x and h_prev side by side, over save_c
+                    // and xc (after the loop, before the rows of dx)
+    float* w_il;    // fp32: [D][4H] W, gate-interleaved columns
+    float* u_il;    // [H][4H] U, likewise
+    float* dwu_il;  // [D + H][4H] weight gradients, gate-interleaved columns
     float* cs_part; // [BWD_CS_CHUNKS][4H] partial column sums of dz
     float* dH;      // [B][H] gradient of h in slot order
     float* dC;      // [B][H]
     float* z;       // [bpad][4H] per-step pre-activations (handles not in per-step mode)
     // bf16 data: fp16 operands of the weight-gradient GEMMs (scaled by powers of two)
     _Float16* dz16; // [B*T][4H]
-    _Float16* x16;  // [B*T][D]
-    _Float16* h16;  // [B*T][H]
+    _Float16* xh16; // [B*T][D + H] x and h_prev
     _Float16* w16;  // [D][4H]
     _Float16* u16;  // [H][4H] U (gate-interleaved), scaled
     _Float16* dzs16;// [B][4H] one step's dz, each row scaled by srow
     float* srow;    // [B] scale of each row's dH
-    unsigned* amax; // [5] largest magnitudes (float bits) of dz, x, h_prev, W, U
-    int32_t* host_offsets;  // pinned [T + 8]: step offsets, the sum of lengths, then amax
+    unsigned* amax; // [BWD_MAX_WORDS] [0..4]: largest magnitudes (float bits) of dz, x, h_prev, W, U
+    int32_t* host_offsets;  // pinned [T + 3]: step offsets, the sum of lengths, the largest |U|
     rocblas_handle rb;
     // the reverse loop in one launch (bf16 data, persistent handles that fit):
     // all steps with column blocks of U (bwdblk.hip), else the steps with few
@@ -797,14 +796,13 @@ static int ensure_train(lstm_dyn* h) {
         return at;
     };
     const long long oh = take(4 * B * T * H), oc = take(4 * B * T * H), ox = take(4 * B * T * D),
-                    ow = take(4 * D * 4 * H), ou = take(4 * H * 4 * H), odw = take(4 * D * 4 * H),
-                    odu = take(4 * H * 4 * H), odb = take(16 * H), odh = take(4 * B * H),
-                    odc = take(4 * B * H), oz = take(16 * H * bpad);
+                    ow = take(4 * D * 4 * H), ou = take(4 * H * 4 * H), odwu = take(4 * (D + H) * 4 * H),
+                    odh = take(4 * B * H), odc = take(4 * B * H), oz = take(16 * H * bpad);
     const bool h16 = h->dtype == LSTM_DYN_BF16;
-    const long long odz16 = take(h16 ? 2 * B * T * 4 * H : 0), ox16 = take(h16 ? 2 * B * T * D : 0),
-                    oh16 = take(h16 ? 2 * B * T * H : 0), ow16 = take(h16 ? 2 * D * 4 * H : 0),
+    const long long odz16 = take(h16 ? 2 * B * T * 4 * H : 0), oxh16 = take(h16 ? 2 * B * T * (D + H) : 0),
+                    ow16 = take(h16 ? 2 * D * 4 * H : 0),
                     ou16 = take(h16 ? 2 * H * 4 * H : 0), odzs = take(h16 ? 2 * B * 4 * H : 0),
-                    osr = take(4 * B), osm = take(256), ocs = take(4LL * BWD_CS_CHUNKS * 4 * H);
+                    osr = take(4 * B), osm = take(4 * BWD_MAX_WORDS), ocs = take(4LL * BWD_CS_CHUNKS * 4 * H);
     const bool pers16 = h16 && h->mode == LSTM_DYN_PERSISTENT;
     if (h->mode == LSTM_DYN_PERSISTENT) (void)xbwd_pick(h->dims, h->num_cus, &tw->xb);
     const bool xb = tw->xb.variant != nullptr;
@@ -836,16 +834,14 @@ static int ensure_train(lstm_dyn* h) {
     tw->xc = reinterpret_cast<float*>(base + ox);
     tw->w_il = reinterpret_cast<float*>(base + ow);
     tw->u_il = reinterpret_cast<float*>(base + ou);
-    tw->dw_il = reinterpret_cast<float*>(base + odw);
-    tw->du_il = reinterpret_cast<float*>(base + odu);
-    tw->db_il = reinterpret_cast<float*>(base + odb);
+    tw->xh = tw->save_c;
+    tw->dwu_il = reinterpret_cast<float*>(base + odwu);
     tw->cs_part = reinterpret_cast<float*>(base + ocs);
     tw->dH = reinterpret_cast<float*>(base + odh);
     tw->dC = reinterpret_cast<float*>(base + odc);
     tw->z = reinterpret_cast<float*>(base + oz);
     tw->dz16 = h16 ? reinterpret_cast<_Float16*>(base + odz16) : nullptr;
-    tw->x16 = h16 ? reinterpret_cast<_Float16*>(base + ox16) : nullptr;
-    tw->h16 = h16 ? reinterpret_cast<_Float16*>(base + oh16) : nullptr;
+    tw->xh16 = h16 ? reinterpret_cast<_Float16*>(base + oxh16) : nullptr;
     tw->w16 = h16 ? reinterpret_cast<_Float16*>(base + ow16) : nullptr;
     tw->u16 = h16 ? reinterpret_cast<_Float16*>(base + ou16) : nullptr;
     tw->dzs16 = h16 ? reinterpret_cast<_Float16*>(base + odzs) : nullptr;
@@ -857,7 +853,7 @@ static int ensure_train(lstm_dyn* h) {
     tw->xus = xb ? reinterpret_cast<float*>(base + oxus) : nullptr;
     tw->pdh = tw->block_groups ? reinterpret_cast<float*>(base + opdh) : nullptr;
     tw->bar = tw->loop_groups || xb ? reinterpret_cast<unsigned*>(base + obar) : nullptr;
-    if (hipHostMalloc(reinterpret_cast<void**>(&tw->host_offsets), (size_t)(T + 8) * sizeof(int32_t),
+    if (hipHostMalloc(reinterpret_cast<void**>(&tw->host_offsets), (size_t)(T + 3) * sizeof(int32_t),
                       hipHostMallocDefault) != hipSuccess) {
         (void)hipFree(tw->block);
         delete tw;
@@ -1053,12 +1049,13 @@ extern "C" int lstm_dyn_backward(lstm_dyn_t* h, const void* x, const int32_t* le
         if ((call) != rocblas_status_success) return LSTM_DYN_ERR_HIP; \
     } while (0)
     RB_CHECK(g_rb.set_stream(tw->rb, s));
-    LD_CHECK(launch_bwd_weights(d, W, d.D, tw->w_il, s));
-    h->launches_last++;
     const bool xb = tw->xb.variant != nullptr;
+    const long max_rows = (long)d.B * d.T;
     if (xb) {
-        // U for the XCD-grouped reverse loop (and its counters and maxima cleared)
-        LD_CHECK(launch_xbwd_pack(d, tw->xb, U, tw->xux, tw->xus, tw->bar, tw->amax, s));
+        // U for the XCD-grouped reverse loop (and its counters and maxima
+        // cleared, the sum of lengths to the host)
+        LD_CHECK(launch_xbwd_pack(d, tw->xb, U, tw->xux, tw->xus, tw->bar, tw->amax, h->ws.meta,
+                                  tw->host_offsets + d.T + 1, s));
         h->launches_last++;
     } else {
         LD_CHECK(launch_bwd_weights(d, U, d.H, tw->u_il, s));
@@ -1070,19 +1067,23 @@ extern "C" int lstm_dyn_backward(lstm_dyn_t* h, const void* x, const int32_t* le
                                     hipMemcpyDeviceToHost, s));
             h->launches_last++;
         }
+        // step offsets (where the host issues the steps) and the sum of lengths
+        // of the forward, on the host
         LD_CHECK(hipMemcpyAsync(tw->host_offsets, h->ws.offsets, (size_t)(d.T + 1) * sizeof(int32_t),
                                 hipMemcpyDeviceToHost, s));
+        LD_CHECK(hipMemcpyAsync(tw->host_offsets + d.T + 1, &h->ws.meta->total_rows, sizeof(int32_t),
+                                hipMemcpyDeviceToHost, s));
+        LD_CHECK(hipMemcpyAsync(h->host_maxlen, &h->ws.meta->max_len, sizeof(int32_t),
+                                hipMemcpyDeviceToHost, s));
     }
-    // step offsets (where the host issues the steps) and the sum of lengths of
-    // the forward, on the host
-    LD_CHECK(hipMemcpyAsync(tw->host_offsets + d.T + 1, &h->ws.meta->total_rows, sizeof(int32_t),
-                            hipMemcpyDeviceToHost, s));
-    LD_CHECK(hipMemcpyAsync(h->host_maxlen, &h->ws.meta->max_len, sizeof(int32_t),
-                            hipMemcpyDeviceToHost, s));
+    if (xb) LD_CHECK(hipEventRecord(tw->copied, s));
+    if (d.bf16) {
+        LD_CHECK(launch_bwd_operands(d, x, W, tw->save_h, max_rows, tw->xh16, tw->w16, tw->amax, h->ws, s));
+        h->launches_last += 2;
+    }
     if (xb) {
         // the loop needs nothing of the host: it runs while the host waits for
-        // the copies only
-        LD_CHECK(hipEventRecord(tw->copied, s));
+        // the sum of lengths only and issues what follows
         LD_CHECK(launch_xbwd(d, tw->xb, tw->xux, d.bf16 ? tw->xus : nullptr, tw->save_h, tw->save_c, d_seq,
                              d_out_h, d_out_c, dh0, dc0, tw->dzx, tw->dzs, tw->amax + 0, tw->bar,
                              h->timeout_ticks, h->trace, h->ws, s));
@@ -1092,7 +1093,7 @@ extern "C" int lstm_dyn_backward(lstm_dyn_t* h, const void* x, const int32_t* le
         LD_CHECK(hipStreamSynchronize(s));
     }
     const int32_t* off = tw->host_offsets;
-    const int rows = off[d.T + 1], max_len = *h->host_maxlen;
+    const int rows = off[d.T + 1], max_len = xb ? 0 : *h->host_maxlen;
     const float one = 1.0f, zero = 0.0f;
     if (!xb) {
         LD_CHECK(launch_bwd_init(d, d_out_h, d_out_c, tw->dH, tw->dC, h->ws, s));
@@ -1164,78 +1165,41 @@ extern "C" int lstm_dyn_backward(lstm_dyn_t* h, const void* x, const int32_t* le
         h->launches_last++;
     }
     if (rows > 0) {
-        // (bf16: the largest |x| of the rows for x's fp16 scale, in the same pass)
-        LD_CHECK(launch_bwd_gather_x(d, x, rows, tw->xc, d.bf16 ? tw->amax + 1 : nullptr, h->ws, s));
-        h->launches_last++;
+        // dW and dU in one GEMM, [X | H_prev]^T dz, then dx rows = dz W^T (K =
+        // the sum of lengths); db = dz^T 1.  bf16 data: the same on fp16
+        // operands, each scaled by a power of two, fp32 accumulation.
+        const int DH = d.D + d.H;
         if (!d.bf16) {
-            // db = dz^T 1 (K = the sum of lengths)
-            LD_CHECK(launch_bwd_colsum(h->ws.gx, rows, H4, tw->cs_part, tw->db_il, nullptr, 1.0f, s));
-            h->launches_last += 2;
-            // dW = X^T dz, dU = H_prev^T dz, then dx rows = dz W^T over the gathered x
-            RB_CHECK(g_rb.sgemm(tw->rb, rocblas_operation_none, rocblas_operation_transpose, H4,
-                                   d.D, rows, &one, h->ws.gx, H4, tw->xc, d.D, &zero, tw->dw_il, H4));
-            RB_CHECK(g_rb.sgemm(tw->rb, rocblas_operation_none, rocblas_operation_transpose, H4,
-                                   d.H, rows, &one, h->ws.gx, H4, tw->save_h, d.H, &zero, tw->du_il,
-                                   H4));
+            LD_CHECK(launch_bwd_operands(d, x, W, tw->save_h, max_rows, tw->xh, tw->w_il, nullptr, h->ws, s));
+            LD_CHECK(launch_bwd_colsum(h->ws.gx, rows, H4, tw->cs_part, nullptr, nullptr, s));
+            RB_CHECK(g_rb.sgemm(tw->rb, rocblas_operation_none, rocblas_operation_transpose, H4, DH,
+                                   rows, &one, h->ws.gx, H4, tw->xh, DH, &zero, tw->dwu_il, H4));
             RB_CHECK(g_rb.sgemm(tw->rb, rocblas_operation_transpose, rocblas_operation_none, d.D,
                                    rows, H4, &one, tw->w_il, H4, h->ws.gx, H4, &zero, tw->xc, d.D));
-            h->launches_last += 3;
+            h->launches_last += 4;
         } else {
-            // bf16 data: the same GEMMs on fp16 operands, each scaled by a power
-            // of two (its largest magnitude into [2^13, 2^14)), fp32 accumulation,
-            // alpha undoing the scales
-            const long n_dz = (long)rows * H4, n_x = (long)rows * d.D, n_h = (long)rows * d.H,
-                       n_w = (long)d.D * H4;
-            // (the one-launch loops took the largest |dz| as they went, and the
-            // gather of x its largest |x|)
-            if (!tw->block_groups && !xb) LD_CHECK(launch_bwd_absmax(h->ws.gx, n_dz, tw->amax + 0, s));
-            LD_CHECK(launch_bwd_absmax(tw->save_h, n_h, tw->amax + 2, s));
-            LD_CHECK(launch_bwd_absmax(tw->w_il, n_w, tw->amax + 3, s));
-            unsigned* am = reinterpret_cast<unsigned*>(tw->host_offsets + d.T + 3);
-            LD_CHECK(hipMemcpyAsync(am, tw->amax, 4 * sizeof(unsigned), hipMemcpyDeviceToHost, s));
-            LD_CHECK(hipStreamSynchronize(s));
-            const float sz = f16_scale(am[0]), sx = f16_scale(am[1]), sh = f16_scale(am[2]),
-                        sw = f16_scale(am[3]);
-            // db and the fp16 dz in one pass over dz
-            LD_CHECK(launch_bwd_colsum(h->ws.gx, rows, H4, tw->cs_part, tw->db_il, tw->dz16, sz, s));
-            LD_CHECK(launch_bwd_to_f16(tw->xc, tw->x16, n_x, sx, s));
-            LD_CHECK(launch_bwd_to_f16(tw->save_h, tw->h16, n_h, sh, s));
-            LD_CHECK(launch_bwd_to_f16(tw->w_il, tw->w16, n_w, sw, s));
+            // (the one-launch loops took the largest |dz| as they went)
+            if (!tw->block_groups && !xb) {
+                LD_CHECK(launch_bwd_absmax(h->ws.gx, (long)rows * H4, tw->amax + 0, s));
+                h->launches_last++;
+            }
+            LD_CHECK(launch_bwd_colsum(h->ws.gx, rows, H4, tw->cs_part, tw->dz16, tw->amax + 0, s));
             const rocblas_datatype f16 = rocblas_datatype_f16_r, f32 = rocblas_datatype_f32_r;
-            const float a_w = 1.0f / (sz * sx), a_u = 1.0f / (sz * sh), a_x = 1.0f / (sz * sw);
             RB_CHECK(g_rb.gemm_ex(tw->rb, rocblas_operation_none, rocblas_operation_transpose, H4,
-                                     d.D, rows, &a_w, tw->dz16, f16, H4, tw->x16, f16, d.D, &zero,
-                                     tw->dw_il, f32, H4, tw->dw_il, f32, H4, f32,
-                                     rocblas_gemm_algo_standard, 0, 0));
-            RB_CHECK(g_rb.gemm_ex(tw->rb, rocblas_operation_none, rocblas_operation_transpose, H4,
-                                     d.H, rows, &a_u, tw->dz16, f16, H4, tw->h16, f16, d.H, &zero,
-                                     tw->du_il, f32, H4, tw->du_il, f32, H4, f32,
+                                     DH, rows, &one, tw->dz16, f16, H4, tw->xh16, f16, DH, &zero,
+                                     tw->dwu_il, f32, H4, tw->dwu_il, f32, H4, f32,
                                      rocblas_gemm_algo_standard, 0, 0));
             RB_CHECK(g_rb.gemm_ex(tw->rb, rocblas_operation_transpose, rocblas_operation_none, d.D,
-                                     rows, H4, &a_x, tw->w16, f16, H4, tw->dz16, f16, H4, &zero,
+                                     rows, H4, &one, tw->w16, f16, H4, tw->dz16, f16, H4, &zero,
                                      tw->xc, f32, d.D, tw->xc, f32, d.D, f32,
                                      rocblas_gemm_algo_standard, 0, 0));
-            h->launches_last += tw->block_groups || xb ? 10 : 11;
+            h->launches_last += 3;
         }
-    } else {
-        LD_CHECK(hipMemsetAsync(tw->dw_il, 0, (size_t)d.D * H4 * sizeof(float), s));
-        LD_CHECK(hipMemsetAsync(tw->du_il, 0, (size_t)d.H * H4 * sizeof(float), s));
-        LD_CHECK(hipMemsetAsync(tw->db_il, 0, (size_t)H4 * sizeof(float), s));
     }
-    if (!packed) {
-        LD_CHECK(launch_bwd_permute(d, tw->dw_il, dW, d.D, s));
-        LD_CHECK(launch_bwd_permute(d, tw->du_il, dU, d.H, s));
-        LD_CHECK(launch_bwd_permute(d, tw->db_il, db, 1, s));
-    } else {
-        // from the four blocks to the cell's layout; the GRU's two bias vectors
-        // take the input and the recurrent side of the packed bias gradient
-        LD_CHECK(launch_bwd_unpack(d, tw->dw_il, dW, d.D, 0, s));
-        LD_CHECK(launch_bwd_unpack(d, tw->du_il, dU, d.H, 1, s));
-        LD_CHECK(launch_bwd_unpack(d, tw->db_il, db, 1, 0, s));
-        if (h->cell == LSTM_DYN_CELL_GRU) LD_CHECK(launch_bwd_unpack(d, tw->db_il, db + 3 * d.H, 1, 1, s));
-    }
-    LD_CHECK(launch_bwd_dx(d, tw->xc, rows, lengths, dx, h->ws, s));
-    h->launches_last += 4;
+    const unsigned* amax = d.bf16 ? tw->amax : nullptr;
+    LD_CHECK(launch_bwd_grads(d, rows > 0 ? tw->dwu_il : nullptr, tw->cs_part, amax, dW, dU, db, s));
+    LD_CHECK(launch_bwd_dx(d, tw->xc, lengths, amax, dx, h->ws, s));
+    h->launches_last += 2;
 #undef RB_CHECK
 #undef LD_CHECK
     return LSTM_DYN_OK;

@@ -19,9 +19,11 @@
 // below).  After the last step the weight gradients are GEMMs over all
 // compact rows (K = sum of lengths): dW = X^T dz, dU = H_prev^T dz,
 // dx = dz W^T, and db = dz^T 1 a column sum, in gate-interleaved columns,
-// permuted back to the caller's gate blocks at the end.  With bf16 data the
-// three GEMMs take fp16 operands scaled by powers of two (fp32
-// accumulation); with fp32 data they are fp32.
+// permuted back to the caller's gate blocks at the end.  dW and dU are one
+// GEMM over [X | H_prev].  With bf16 data the GEMMs take fp16 operands scaled
+// by powers of two (each operand's largest magnitude into [2^13, 2^14): exact,
+// and far from fp16 overflow; fp32 accumulation; the passes that hand out the
+// results divide the scales out); with fp32 data they are fp32.
 #include "launch.h"
 
 namespace ldyn {
@@ -186,80 +188,246 @@ __global__ void bwd_ones_kernel(float* a, int n) {
     if (i < n) a[i] = 1.0f;
 }
 
-// The workgroup's largest value of m (256 threads) into *out by one atomic
-// maximum: many atomics on one address queue behind each other.
-__device__ inline void block_max_to(unsigned m, unsigned* out) {
+// The workgroup's largest value of m (256 threads), in every thread.
+__device__ inline unsigned block_max(unsigned m) {
     __shared__ unsigned red[4];
     for (int o = 32; o > 0; o >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, o));
+    __syncthreads();  // (an earlier call's readers are done)
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
-    if (threadIdx.x == 0) atomicMax(out, max(max(red[0], red[1]), max(red[2], red[3])));
+    return max(max(red[0], red[1]), max(red[2], red[3]));
 }
 
-// x rows in the compact order, fp32, one wave per row (VEC: four elements
-// per lane and load, D a multiple of 4 and x aligned to four elements).  With
-// amax, the largest |x| of those rows (as bits) goes there too.
+// The power of two that brings a largest magnitude (float bits) into
+// [2^13, 2^14): fp16 keeps its 11 bits there, far from overflow.  1 for zero,
+// infinity and NaN.
+__device__ inline float f16_scale_of(unsigned bits) {
+    if (bits == 0u || !(__uint_as_float(bits) < 3.0e38f)) return 1.0f;
+    return __uint_as_float((unsigned)(127 + min(140 - (int)(bits >> 23), 126)) << 23);
+}
+
+// 1 / a power of two within [2^-126, 2^126]: exact.
+__device__ inline float pow2_inverse(float s) {
+    return __uint_as_float((254u << 23) - __float_as_uint(s));
+}
+
+// Operands of the GEMMs over all compact rows, which need nothing of the
+// reverse loop: xh [rows][D + H], each row's x and the h its step started from
+// side by side (one GEMM then gives dW and dU: with one each, the 512 x 2048
+// outputs at H = D = 512 are 64 tiles for 256 CUs and took 51 us apiece), and
+// w [D][4H], W with gate-interleaved columns.  With bf16 data they are fp16,
+// scaled from amax: a pass for the largest magnitudes, then this one, each one
+// launch (they read 2 to 4 bytes per element once and are bound by memory at
+// large sizes, by their launches at small ones).
+struct OperandParams {
+    const void* x;          // [B*T][D]
+    const void* W;          // [D][4H], gate blocks
+    const float* save_h;    // [rows][H]
+    const int32_t* rowsrc;  // compact row -> b * T + t
+    const Meta* meta;
+    unsigned* amax;         // [1] |x|, [2] |h|, [3] |W| (float bits)
+    void* xh;
+    void* w;
+    int D, H;
+    unsigned* part;         // [3][BWD_MAX_PARTS] each workgroup's largest of one of them
+    int parts;              // workgroups per operand
+};
+
+__device__ inline unsigned abs_bits(float v) { return __float_as_uint(v) & 0x7fffffffu; }
+
+// Largest |a[i]| (as bits) of the thread's share of n floats, a 16-byte
+// aligned: four elements per load, four loads in flight, then the tail.
+__device__ inline unsigned absmax_share(const float* __restrict__ a, long n) {
+    unsigned m = 0;
+    const long n4 = n >> 2, stride = (long)gridDim.x * 256;
+    long i = blockIdx.x * 256L + threadIdx.x;
+    for (; i + 3 * stride < n4; i += 4 * stride) {
+        f32x4_t v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = reinterpret_cast<const f32x4_t*>(a)[i + j * stride];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) m = max(m, abs_bits(v[j][e]));
+    }
+    for (; i < n4; i += stride) {
+        const f32x4_t v = reinterpret_cast<const f32x4_t*>(a)[i];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m = max(m, abs_bits(v[e]));
+    }
+    for (long k = 4 * n4 + blockIdx.x * 256L + threadIdx.x; k < n; k += stride) m = max(m, abs_bits(a[k]));
+    return m;
+}
+
+// The largest |x|, |h| and |W| of each workgroup's share, a third of the
+// workgroups on each.  VEC: four elements of x and W per load (D a multiple of
+// 4, x and W aligned to four elements).  Four loads in flight per thread; no
+// atomics, which at 1536 on one line queued for longer than the reads take (18
+// MB at H = D = 512 and 6400 rows: 20 us with them, 6.5 us so).
 template <typename S, bool VEC>
 __global__ void __launch_bounds__(256)
-bwd_gather_x_kernel(const S* __restrict__ x, const int32_t* __restrict__ rowsrc,
-                    const Meta* __restrict__ meta, float* __restrict__ xc, int D, unsigned* amax) {
-    const long rows = meta->total_rows;
-    const int lane = threadIdx.x & 63;
+bwd_operand_max_kernel(OperandParams p) {
+    constexpr int V = VEC ? 4 : 1;
+    typedef S v_t __attribute__((ext_vector_type(V)));
+    const long rows = p.meta->total_rows;
     unsigned m = 0;
-    for (long r = blockIdx.x * 4L + (threadIdx.x >> 6); r < rows; r += gridDim.x * 4L) {
-        const S* src = x + (long)rowsrc[r] * D;
-        float* dst = xc + r * D;
-        if constexpr (VEC) {
-            typedef S s4_t __attribute__((ext_vector_type(4)));
-#pragma unroll 4
-            for (int k = lane; k < D / 4; k += 64) {
-                const s4_t v = reinterpret_cast<const s4_t*>(src)[k];
-                const f32x4_t f = f32x4_t{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
-                reinterpret_cast<f32x4_t*>(dst)[k] = f;
+    if (blockIdx.y == 0) {
+        const int lane = threadIdx.x & 63, nk = p.D / V;
+        for (long r = blockIdx.x * 16L + (threadIdx.x >> 6) * 4; r < rows; r += gridDim.x * 16L) {
+            const v_t* src[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) m = max(m, __float_as_uint(f[e]) & 0x7fffffffu);
+            for (int j = 0; j < 4; ++j)  // (past the end: the first of the four again)
+                src[j] = reinterpret_cast<const v_t*>(static_cast<const S*>(p.x) +
+                                                      (long)p.rowsrc[r + j < rows ? r + j : r] * p.D);
+            for (int k = lane; k < nk; k += 64) {
+                v_t v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) v[j] = src[j][k];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int e = 0; e < V; ++e) m = max(m, abs_bits((float)v[j][e]));
+            }
+        }
+    } else if (blockIdx.y == 1) {
+        m = absmax_share(p.save_h, rows * p.H);
+    } else {
+        const v_t* w = static_cast<const v_t*>(p.W);
+        const long nw = (long)p.D * 4 * p.H / V;
+#pragma unroll 4
+        for (long i = blockIdx.x * 256L + threadIdx.x; i < nw; i += gridDim.x * 256L) {
+            const v_t v = w[i];
+#pragma unroll
+            for (int e = 0; e < V; ++e) m = max(m, abs_bits((float)v[e]));
+        }
+    }
+    m = block_max(m);
+    if (threadIdx.x == 0) p.part[blockIdx.y * BWD_MAX_PARTS + blockIdx.x] = m;
+}
+
+// xh and w.  One wave per row of either.  O: their type (_Float16: scaled from
+// the largest magnitudes, which also go to amax).  VEC: D and H multiples of 4, x aligned to four elements.
+template <typename S, typename O, bool VEC>
+__global__ void __launch_bounds__(256)
+bwd_operands_kernel(OperandParams p) {
+    constexpr int V = VEC ? 4 : 1;
+    constexpr bool SCALED = sizeof(O) == 2;
+    typedef S s_t __attribute__((ext_vector_type(V)));
+    typedef float f_t __attribute__((ext_vector_type(V)));
+    typedef O o_t __attribute__((ext_vector_type(V)));
+    typedef O o4_t __attribute__((ext_vector_type(4)));
+    const long rows = p.meta->total_rows, all = rows + p.D;
+    const int lane = threadIdx.x & 63, D = p.D, H = p.H;
+    float sx = 1.0f, sh = 1.0f, sw = 1.0f;
+    if constexpr (SCALED) {
+        unsigned m[3] = {0u, 0u, 0u};
+        for (int i = threadIdx.x; i < p.parts; i += 256)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) m[j] = max(m[j], p.part[j * BWD_MAX_PARTS + i]);
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            m[j] = block_max(m[j]);
+            if (blockIdx.x == 0 && threadIdx.x == 0) p.amax[1 + j] = m[j];
+        }
+        sx = f16_scale_of(m[0]);
+        sh = f16_scale_of(m[1]);
+        sw = f16_scale_of(m[2]);
+    }
+    for (long r = blockIdx.x * 4L + (threadIdx.x >> 6); r < all; r += gridDim.x * 4L) {
+        if (r < rows) {
+            const s_t* src = reinterpret_cast<const s_t*>(static_cast<const S*>(p.x) + (long)p.rowsrc[r] * D);
+            const f_t* hr = reinterpret_cast<const f_t*>(p.save_h + r * H);
+            o_t* dst = reinterpret_cast<o_t*>(static_cast<O*>(p.xh) + r * (D + H));
+            o_t* dsth = reinterpret_cast<o_t*>(static_cast<O*>(p.xh) + r * (D + H) + D);
+#pragma unroll 4
+            for (int k = lane; k < D / V; k += 64) {
+                const s_t v = src[k];
+                o_t o;
+#pragma unroll
+                for (int e = 0; e < V; ++e) o[e] = (O)((float)v[e] * sx);
+                dst[k] = o;
+            }
+#pragma unroll 4
+            for (int k = lane; k < H / V; k += 64) {
+                const f_t v = hr[k];
+                o_t o;
+#pragma unroll
+                for (int e = 0; e < V; ++e) o[e] = (O)(v[e] * sh);
+                dsth[k] = o;
             }
         } else {
+            const long k = r - rows;
+            const S* src = static_cast<const S*>(p.W) + k * 4 * H;
+            o4_t* dst = reinterpret_cast<o4_t*>(static_cast<O*>(p.w) + k * 4 * H);
 #pragma unroll 4
-            for (int k = lane; k < D; k += 64) {
-                const float f = (float)src[k];
-                dst[k] = f;
-                m = max(m, __float_as_uint(f) & 0x7fffffffu);
+            for (int u = lane; u < H; u += 64) {
+                o4_t o;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) o[g] = (O)((float)src[g * H + u] * sw);
+                dst[u] = o;
             }
         }
     }
-    if (amax) block_max_to(m, amax);
 }
 
-// Interleaved columns -> the caller's gate blocks: out[k][g H + u] = il[k][4u + g].
-__global__ void __launch_bounds__(256)
-bwd_permute_kernel(const float* __restrict__ il, float* out, int rows, int H) {
-    const long n = (long)rows * 4 * H;
-    for (long i = blockIdx.x * 256L + threadIdx.x; i < n; i += (long)gridDim.x * 256) {
-        const long k = i / (4 * H);
-        const int cp = (int)(i - k * 4 * H);
-        out[k * 4 * H + gate_col(cp, H)] = il[i];
+// The cell's gradients from gate-interleaved columns c' = 4u + g.  Block j of
+// the caller's layout comes from gate src(j); part: 0 the input side (W, b_ih
+// or b), 1 the recurrent side (U, b_hh).  (The packed four-block layout of GRU:
+// r, u, then the recurrent part of n, then its input part; RNN: one block.)
+template <int CELL>
+struct GradCols {
+    static constexpr int N = CELL == CELL_LSTM ? 4 : CELL == CELL_GRU ? 3 : 1;
+    static __device__ constexpr int src(int part, int j) {
+        return CELL == CELL_GRU && j == 2 ? (part == 0 ? 3 : 2) : j;
     }
-}
+};
 
-// GRU and RNN gradients from the packed four-block layout (gate-interleaved
-// columns c' = 4u + g) to the cell's own: block g of column j of the output
-// comes from interleaved column 4u + src(g).  part: 0 the input side (W, b_ih
-// or b), 1 the recurrent side (U, b_hh).
-__device__ inline int unpack_src(int cell, int part, int g) {
-    if (cell == CELL_RNN) return 0;
-    if (g < 2) return g;               // r, u
-    return part == 0 ? 3 : 2;          // n: input part in block 3, recurrent in block 2
-}
-
+// dW, dU and db in one launch: il [(D + H)][4H] (rows of dW, then of dU; null:
+// no compact row, all zero) to the caller's columns, one wave per row, the
+// fp16 scales of the operands (amax, or null) divided out; db from the
+// BWD_CS_CHUNKS partial sums in order, one unit per lane, by the first
+// workgroups.
+template <int CELL>
 __global__ void __launch_bounds__(256)
-bwd_unpack_kernel(const float* __restrict__ il, float* out, int rows, int H, int cell, int part) {
-    const int G = cell == CELL_GRU ? 3 * H : H;
-    const long n = (long)rows * G;
-    for (long i = blockIdx.x * 256L + threadIdx.x; i < n; i += (long)gridDim.x * 256) {
-        const long k = i / G;
-        const int j = (int)(i - k * G), g = j / H, u = j - g * H;
-        out[i] = il[k * 4 * H + 4 * u + unpack_src(cell, part, g)];
+bwd_grads_kernel(const float* __restrict__ il, const float* __restrict__ part,
+                 const unsigned* __restrict__ amax, float* dW, float* dU, float* db, int D, int H,
+                 int db_blocks) {
+    using GC = GradCols<CELL>;
+    if ((int)blockIdx.x < db_blocks) {
+        const int u = blockIdx.x * 256 + threadIdx.x;
+        if (u >= H) return;
+        f32x4_t s = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        if (il) {
+#pragma unroll 16
+            for (int k = 0; k < BWD_CS_CHUNKS; ++k)
+                s += *reinterpret_cast<const f32x4_t*>(part + ((size_t)k * H + u) * 4);
+        }
+#pragma unroll
+        for (int j = 0; j < GC::N; ++j) {
+            db[(size_t)j * H + u] = s[GC::src(0, j)];
+            if constexpr (CELL == CELL_GRU) db[(size_t)(GC::N + j) * H + u] = s[GC::src(1, j)];
+        }
+        return;
+    }
+    const int lane = threadIdx.x & 63;
+    const float isz = amax ? pow2_inverse(f16_scale_of(amax[0])) : 1.0f;
+    const float iw = amax ? pow2_inverse(f16_scale_of(amax[1])) : 1.0f;
+    const float iu = amax ? pow2_inverse(f16_scale_of(amax[2])) : 1.0f;
+    const long step = (long)(gridDim.x - db_blocks) * 4;
+    for (long r = (blockIdx.x - db_blocks) * 4L + (threadIdx.x >> 6); r < D + H; r += step) {
+        const int side = r >= D;
+        float* out = side ? dU + (r - D) * GC::N * H : dW + r * GC::N * H;
+        const float is = side ? iu : iw;
+#pragma unroll 4
+        for (int u = lane; u < H; u += 64) {
+            f32x4_t v = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            if (il) v = *reinterpret_cast<const f32x4_t*>(il + ((size_t)r * H + u) * 4);
+#pragma unroll
+            for (int j = 0; j < GC::N; ++j) {
+                const float w = side ? v[GC::src(1, j)] : v[GC::src(0, j)];
+                out[(size_t)j * H + u] = w * isz * is;
+            }
+        }
     }
 }
 
@@ -271,8 +439,11 @@ bwd_unpack_kernel(const float* __restrict__ il, float* out, int rows, int H, int
 template <bool VEC>
 __global__ void __launch_bounds__(256)
 bwd_dx_kernel(const float* __restrict__ dxc, const int32_t* __restrict__ perm,
-              const int32_t* __restrict__ offsets, const int32_t* __restrict__ lengths, float* dx,
-              int B, int T, int D) {
+              const int32_t* __restrict__ offsets, const int32_t* __restrict__ lengths,
+              const unsigned* __restrict__ amax, float* dx, int B, int T, int D) {
+    // (fp16 operands: the scales of dz and W are divided out here)
+    const float iz = amax ? pow2_inverse(f16_scale_of(amax[0])) : 1.0f;
+    const float iw = amax ? pow2_inverse(f16_scale_of(amax[3])) : 1.0f;
     extern __shared__ int32_t slot_of[];  // [B] batch row -> slot
     for (int i = threadIdx.x; i < B; i += 256) slot_of[perm[i]] = i;
     __syncthreads();
@@ -286,55 +457,32 @@ bwd_dx_kernel(const float* __restrict__ dxc, const int32_t* __restrict__ perm,
         if constexpr (VEC) {
             for (int k = lane; k < D / 4; k += 64)
                 reinterpret_cast<f32x4_t*>(dst)[k] =
-                    runs ? reinterpret_cast<const f32x4_t*>(src)[k] : f32x4_t{0.f, 0.f, 0.f, 0.f};
+                    runs ? reinterpret_cast<const f32x4_t*>(src)[k] * iz * iw : f32x4_t{0.f, 0.f, 0.f, 0.f};
         } else {
-            for (int k = lane; k < D; k += 64) dst[k] = runs ? src[k] : 0.0f;
+            for (int k = lane; k < D; k += 64) dst[k] = runs ? src[k] * iz * iw : 0.0f;
         }
     }
 }
 
 // ---------------------------------------------------------------------------
-// fp16 operands for the GEMMs of the backward with bf16 data: each operand is
-// scaled by a power of two that brings its largest magnitude to [2^13, 2^14)
-// (exact, and far from fp16 overflow; the host picks it from the largest
-// magnitude), and the GEMM's alpha undoes the scales.
-
 // Largest |a| of n floats (as bits): the bits of non-negative floats order as
 // integers, so an integer atomic maximum gives the same result in any order.
-// a is 16-byte aligned: four elements per load, then the tail.
 __global__ void __launch_bounds__(256)
 bwd_absmax_kernel(const float* __restrict__ a, long n, unsigned* out) {
-    unsigned m = 0;
-    const long n4 = n >> 2, stride = (long)gridDim.x * 256;
-    long i = blockIdx.x * 256L + threadIdx.x;
-    for (; i + 3 * stride < n4; i += 4 * stride) {  // four loads in flight
-        f32x4_t v[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = reinterpret_cast<const f32x4_t*>(a)[i + j * stride];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) m = max(m, __float_as_uint(v[j][e]) & 0x7fffffffu);
-    }
-    for (; i < n4; i += stride) {
-        const f32x4_t v = reinterpret_cast<const f32x4_t*>(a)[i];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) m = max(m, __float_as_uint(v[e]) & 0x7fffffffu);
-    }
-    for (long i = 4 * n4 + blockIdx.x * 256L + threadIdx.x; i < n; i += (long)gridDim.x * 256)
-        m = max(m, __float_as_uint(a[i]) & 0x7fffffffu);
-    block_max_to(m, out);
+    const unsigned m = block_max(absmax_share(a, n));
+    if (threadIdx.x == 0) atomicMax(out, m);
 }
 
 // db = dz^T 1 over all compact rows: the rows are cut into BWD_CS_CHUNKS
 // ranges, a thread sums one group of four columns over one range in row
-// order (partial sums, then bwd_colsum_finish_kernel over the ranges in
-// order), and with CONV the same pass writes dz16 = fp16(dz * scale) for
+// order (partial sums, which bwd_grads_kernel adds in the order of the
+// ranges), and with CONV the same pass writes dz16 = fp16(dz * scale from *amax) for
 // the weight-gradient GEMMs.
 template <bool CONV>
 __global__ void __launch_bounds__(256)
 bwd_colsum_kernel(const float* __restrict__ dz, long rows, int n4, float* __restrict__ part,
-                  _Float16* __restrict__ dz16, float scale) {
+                  _Float16* __restrict__ dz16, const unsigned* __restrict__ amax) {
+    const float scale = CONV ? f16_scale_of(*amax) : 1.0f;
     const int cg = blockIdx.x * 256 + threadIdx.x;  // columns 4 cg .. 4 cg + 3
     if (cg >= n4) return;
     const long per = (rows + BWD_CS_CHUNKS - 1) / BWD_CS_CHUNKS;
@@ -351,15 +499,6 @@ bwd_colsum_kernel(const float* __restrict__ dz, long rows, int n4, float* __rest
                      (_Float16)(v[3] * scale)};
     }
     *reinterpret_cast<f32x4_t*>(part + (size_t)blockIdx.y * 4 * n4 + 4 * cg) = acc;
-}
-
-__global__ void __launch_bounds__(256)
-bwd_colsum_finish_kernel(const float* __restrict__ part, int ncols, float* __restrict__ out) {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= ncols) return;
-    float s = 0.0f;
-    for (int k = 0; k < BWD_CS_CHUNKS; ++k) s += part[(size_t)k * ncols + c];
-    out[c] = s;
 }
 
 // dst = fp16(src * scale), n elements (both 16-byte aligned: four elements per
@@ -414,14 +553,6 @@ hipError_t launch_bwd_cell(const Dims& d, int t, int off, int act, const float* 
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_unpack(const Dims& d, const float* il, float* out, int rows, int part,
-                             hipStream_t s) {
-    const long n = (long)rows * (d.cell == CELL_GRU ? 3 : 1) * d.H;
-    hipLaunchKernelGGL(bwd_unpack_kernel, dim3(grid_of(n)), dim3(256), 0, s, il, out, rows, d.H,
-                       d.cell, part);
-    return hipGetLastError();
-}
-
 hipError_t launch_bwd_state_out(const Dims& d, const float* dH, const float* dC, const float* srow,
                                 float* dh0, float* dc0, const Workspace& ws, hipStream_t s) {
     hipLaunchKernelGGL(bwd_state_out_kernel, dim3(grid_of((long)d.B * d.H)), dim3(256), 0, s, dH,
@@ -445,28 +576,42 @@ hipError_t launch_bwd_ones(float* a, int n, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_gather_x(const Dims& d, const void* x, long rows, float* xc, unsigned* amax,
-                               const Workspace& ws, hipStream_t s) {
-    const long g4 = (rows + 3) / 4;
-    const unsigned g = (unsigned)(g4 < 1 ? 1 : g4 > 1024 ? 1024 : g4);
-    const uintptr_t xa = reinterpret_cast<uintptr_t>(x);
+hipError_t launch_bwd_operands(const Dims& d, const void* x, const void* W, const float* save_h,
+                               long max_rows, void* xh, void* w, unsigned* amax, const Workspace& ws,
+                               hipStream_t s) {
+    const long g4 = (max_rows + d.D + 3) / 4;
+    const int parts = (int)(g4 > BWD_MAX_PARTS ? BWD_MAX_PARTS : g4);
+    const OperandParams p{x, W, save_h, ws.rowsrc, ws.meta, amax, xh, w, d.D, d.H,
+                          amax ? amax + BWD_MAX_AT : nullptr, parts};
+    const dim3 grid((unsigned)(g4 > 2048 ? 2048 : g4)), gmax((unsigned)parts, 3);
+    const uintptr_t xa = reinterpret_cast<uintptr_t>(x), wa = reinterpret_cast<uintptr_t>(W);
+    const bool v4 = d.D % 4 == 0 && d.H % 4 == 0;
     if (d.bf16) {
-        const __bf16* xs = static_cast<const __bf16*>(x);
-        if (d.D % 4 == 0 && (xa & 7) == 0)
-            hipLaunchKernelGGL((bwd_gather_x_kernel<__bf16, true>), dim3(g), dim3(256), 0, s, xs, ws.rowsrc,
-                               ws.meta, xc, d.D, amax);
+        if (d.D % 4 == 0 && ((xa | wa) & 7) == 0)
+            hipLaunchKernelGGL((bwd_operand_max_kernel<__bf16, true>), gmax, dim3(256), 0, s, p);
         else
-            hipLaunchKernelGGL((bwd_gather_x_kernel<__bf16, false>), dim3(g), dim3(256), 0, s, xs, ws.rowsrc,
-                               ws.meta, xc, d.D, amax);
+            hipLaunchKernelGGL((bwd_operand_max_kernel<__bf16, false>), gmax, dim3(256), 0, s, p);
+        if (v4 && (xa & 7) == 0)
+            hipLaunchKernelGGL((bwd_operands_kernel<__bf16, _Float16, true>), grid, dim3(256), 0, s, p);
+        else
+            hipLaunchKernelGGL((bwd_operands_kernel<__bf16, _Float16, false>), grid, dim3(256), 0, s, p);
     } else {
-        const float* xs = static_cast<const float*>(x);
-        if (d.D % 4 == 0 && (xa & 15) == 0)
-            hipLaunchKernelGGL((bwd_gather_x_kernel<float, true>), dim3(g), dim3(256), 0, s, xs, ws.rowsrc,
-                               ws.meta, xc, d.D, amax);
+        if (v4 && (xa & 15) == 0)
+            hipLaunchKernelGGL((bwd_operands_kernel<float, float, true>), grid, dim3(256), 0, s, p);
         else
-            hipLaunchKernelGGL((bwd_gather_x_kernel<float, false>), dim3(g), dim3(256), 0, s, xs, ws.rowsrc,
-                               ws.meta, xc, d.D, amax);
+            hipLaunchKernelGGL((bwd_operands_kernel<float, float, false>), grid, dim3(256), 0, s, p);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_bwd_grads(const Dims& d, const float* il, const float* part, const unsigned* amax,
+                            float* dW, float* dU, float* db, hipStream_t s) {
+    const int nb = (d.H + 255) / 256;
+    const long g4 = ((long)d.D + d.H + 3) / 4;
+    auto k = d.cell == CELL_GRU ? bwd_grads_kernel<CELL_GRU>
+             : d.cell == CELL_RNN ? bwd_grads_kernel<CELL_RNN> : bwd_grads_kernel<CELL_LSTM>;
+    hipLaunchKernelGGL(k, dim3((unsigned)(nb + (g4 > 2048 ? 2048 : g4))), dim3(256), 0, s, il, part, amax,
+                       dW, dU, db, d.D, d.H, nb);
     return hipGetLastError();
 }
 
@@ -476,17 +621,14 @@ hipError_t launch_bwd_absmax(const float* a, long n, unsigned* out, hipStream_t 
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_colsum(const float* dz, long rows, int ncols, float* part, float* out,
-                             _Float16* dz16, float scale, hipStream_t s) {
+hipError_t launch_bwd_colsum(const float* dz, long rows, int ncols, float* part, _Float16* dz16,
+                             const unsigned* amax, hipStream_t s) {
     const int n4 = ncols / 4;
     const dim3 grid((unsigned)((n4 + 255) / 256), BWD_CS_CHUNKS);
     if (dz16)
-        hipLaunchKernelGGL(bwd_colsum_kernel<true>, grid, dim3(256), 0, s, dz, rows, n4, part, dz16, scale);
+        hipLaunchKernelGGL(bwd_colsum_kernel<true>, grid, dim3(256), 0, s, dz, rows, n4, part, dz16, amax);
     else
-        hipLaunchKernelGGL(bwd_colsum_kernel<false>, grid, dim3(256), 0, s, dz, rows, n4, part, dz16,
-                           scale);
-    hipLaunchKernelGGL(bwd_colsum_finish_kernel, dim3((unsigned)((ncols + 255) / 256)), dim3(256), 0, s,
-                       part, ncols, out);
+        hipLaunchKernelGGL(bwd_colsum_kernel<false>, grid, dim3(256), 0, s, dz, rows, n4, part, dz16, amax);
     return hipGetLastError();
 }
 
@@ -495,24 +637,17 @@ hipError_t launch_bwd_to_f16(const float* src, _Float16* dst, long n, float scal
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_permute(const Dims& d, const float* il, float* out, int rows, hipStream_t s) {
-    hipLaunchKernelGGL(bwd_permute_kernel, dim3(grid_of((long)rows * 4 * d.H)), dim3(256), 0, s, il,
-                       out, rows, d.H);
-    return hipGetLastError();
-}
-
-hipError_t launch_bwd_dx(const Dims& d, const float* dxc, long rows, const int32_t* lengths,
+hipError_t launch_bwd_dx(const Dims& d, const float* dxc, const int32_t* lengths, const unsigned* amax,
                          float* dx, const Workspace& ws, hipStream_t s) {
-    (void)rows;
     const long g4 = ((long)d.B * d.T + 3) / 4;
     const unsigned g = (unsigned)(g4 < 1 ? 1 : g4 > 4096 ? 4096 : g4);
     const size_t lds = (size_t)d.B * sizeof(int32_t);
     if (d.D % 4 == 0 && (reinterpret_cast<uintptr_t>(dx) & 15) == 0)
         hipLaunchKernelGGL(bwd_dx_kernel<true>, dim3(g), dim3(256), lds, s, dxc, ws.perm, ws.offsets, lengths,
-                           dx, d.B, d.T, d.D);
+                           amax, dx, d.B, d.T, d.D);
     else
         hipLaunchKernelGGL(bwd_dx_kernel<false>, dim3(g), dim3(256), lds, s, dxc, ws.perm, ws.offsets, lengths,
-                           dx, d.B, d.T, d.D);
+                           amax, dx, d.B, d.T, d.D);
     return hipGetLastError();
 }
 

@@ -161,10 +161,6 @@ hipError_t launch_bwd_cell(const Dims& d, int t, int off, int act, const float* 
                            const float* save_c,
                            const float* dseq, float* dH, float* dC, const Workspace& ws,
                            hipStream_t s);
-// GRU/RNN gradients, packed four-block (interleaved) layout -> the cell's own;
-// part 0: input side (W, b_ih / b), 1: recurrent side (U, b_hh).
-hipError_t launch_bwd_unpack(const Dims& d, const float* il, float* out, int rows, int part,
-                             hipStream_t s);
 hipError_t launch_bwd_state_out(const Dims& d, const float* dH, const float* dC, const float* srow,
                                 float* dh0, float* dc0, const Workspace& ws, hipStream_t s);
 // bf16 data: the cell's backward with one workgroup per row, also writing the
@@ -207,8 +203,9 @@ hipError_t launch_bwd_block(const Dims& d, const _Float16* u16, float alpha_u, c
 // handles where all of U fits the CUs of one XCD: one cooperative launch for
 // every step, dh0 and dc0 written to the caller's buffers.  xbwd_pick: false
 // where it does not apply.  launch_xbwd_pack fills ux (ux_bytes) and us [H]
-// (bf16 data) from U [H][4H] in gate blocks and clears bar and amax [5];
-// dzx and dzs need no contents.
+// (bf16 data) from U [H][4H] in gate blocks, clears bar and amax [5] and puts
+// the forward's sum of lengths into host_rows (pinned); dzx and dzs need no
+// contents.
 struct XBwdConfig {
     const void* variant;  // the compiled variant, or null
     int ng_shift, gsize, rg;  // as in XLoopConfig
@@ -217,27 +214,36 @@ struct XBwdConfig {
 };
 bool xbwd_pick(const Dims& d, int num_cus, XBwdConfig* xb);
 hipError_t launch_xbwd_pack(const Dims& d, const XBwdConfig& xb, const void* U, void* ux, float* us,
-                            unsigned* bar, unsigned* amax, hipStream_t s);
+                            unsigned* bar, unsigned* amax, const Meta* meta, int32_t* host_rows,
+                            hipStream_t s);
 hipError_t launch_xbwd(const Dims& d, const XBwdConfig& xb, const void* ux, const float* us,
                        const float* save_h, const float* save_c, const float* dseq, const float* d_out_h,
                        const float* d_out_c, float* dh0, float* dc0, void* dzx, void* dzs, unsigned* amax_dz,
                        unsigned* bar, unsigned long long timeout_ticks, unsigned long long* trace,
                        const Workspace& ws, hipStream_t s);
-// xc = the compact rows of x in fp32; amax (or null) receives the largest
-// |x| of them, as float bits, by atomic maximum.
-hipError_t launch_bwd_gather_x(const Dims& d, const void* x, long rows, float* xc, unsigned* amax,
-                               const Workspace& ws, hipStream_t s);
-// fp16 operands of the backward's GEMMs: the largest magnitude (as float bits,
-// atomic and order free) and a scaled conversion.
+// Operands of the GEMMs over all compact rows: xh [rows][D + H] (x, then the h
+// each step started from) and w [D][4H] (gate-interleaved), fp32, or fp16 with
+// bf16 data: scaled from amax[1..3] (|x|, |h|, |W| as float bits), which this
+// fills (two launches).  amax has BWD_MAX_WORDS words, those from BWD_MAX_AT on
+// for its use.  max_rows: B * T (grid sizes only).
+constexpr int BWD_MAX_PARTS = 512, BWD_MAX_AT = 64, BWD_MAX_WORDS = BWD_MAX_AT + 3 * BWD_MAX_PARTS;
+hipError_t launch_bwd_operands(const Dims& d, const void* x, const void* W, const float* save_h,
+                               long max_rows, void* xh, void* w, unsigned* amax, const Workspace& ws,
+                               hipStream_t s);
+// Largest magnitude (as float bits, atomic and order free), a scaled conversion.
 hipError_t launch_bwd_absmax(const float* a, long n, unsigned* out, hipStream_t s);
 hipError_t launch_bwd_to_f16(const float* src, _Float16* dst, long n, float scale, hipStream_t s);
-// db = column sums of dz [rows][ncols] (ncols a multiple of 4) through
-// part [BWD_CS_CHUNKS][ncols]; with dz16, also dz16 = fp16(dz * scale).
+// part [BWD_CS_CHUNKS][ncols]: partial column sums of dz [rows][ncols] (ncols a
+// multiple of 4); with dz16, also dz16 = fp16(dz scaled from *amax).
 constexpr int BWD_CS_CHUNKS = 64;
-hipError_t launch_bwd_colsum(const float* dz, long rows, int ncols, float* part, float* out,
-                             _Float16* dz16, float scale, hipStream_t s);
-hipError_t launch_bwd_permute(const Dims& d, const float* il, float* out, int rows, hipStream_t s);
-hipError_t launch_bwd_dx(const Dims& d, const float* dxc, long rows, const int32_t* lengths,
+hipError_t launch_bwd_colsum(const float* dz, long rows, int ncols, float* part, _Float16* dz16,
+                             const unsigned* amax, hipStream_t s);
+// dW, dU, db in the cell's own layout from il [(D + H)][4H] (gate-interleaved;
+// null: no compact row) and part; amax: the fp16 operands' maxima, or null.
+hipError_t launch_bwd_grads(const Dims& d, const float* il, const float* part, const unsigned* amax,
+                            float* dW, float* dU, float* db, hipStream_t s);
+// dx [B][T][D] from its compact rows (amax as above).
+hipError_t launch_bwd_dx(const Dims& d, const float* dxc, const int32_t* lengths, const unsigned* amax,
                          float* dx, const Workspace& ws, hipStream_t s);
 // Forward for training from the saved state: out_seq[b][t] for t < L[b]
 // (the state after step t is the one step t + 1 started from, or out_h).

@@ -67,11 +67,14 @@ bool xbwd_pick(const Dims& d, int num_cus, XBwdConfig* xb) {
 // fp32); chunk q * 16 + r of a block holds row r and the q-th 16 bytes of the
 // run.  One wave per row; fp16 rows are scaled by the power of two that brings
 // their largest magnitude into [2^13, 2^14), us gets its inverse.  Zero past H
-// and past 4H.  The first workgroup also clears the loop's counters and maxima.
+// and past 4H.  The first workgroup also clears the loop's counters and maxima
+// and hands the forward's sum of lengths to the host.  Loads are issued eight
+// at a time: one by one a row's 4H scalars were 32 memory latencies at H = 512
+// (20 us, now 7.5).
 template <typename E>
 __global__ void __launch_bounds__(256)
 xbwd_pack_kernel(const typename E::src_t* __restrict__ U, void* ux, float* us, int H, int urows, int kpad,
-                 unsigned* bar, unsigned* amax) {
+                 unsigned* bar, unsigned* amax, const Meta* meta, int32_t* host_rows) {
     using S = typename E::store_t;
     constexpr int CK = 16 / (int)sizeof(S);  // columns per chunk: CK / 4 units
     typedef S chunk_t __attribute__((ext_vector_type(CK)));
@@ -82,6 +85,7 @@ xbwd_pack_kernel(const typename E::src_t* __restrict__ U, void* ux, float* us, i
             bar[64 * tid + 1] = 0u;
         }
         if (tid < 5) amax[tid] = 0u;
+        if (tid == 64) *host_rows = meta->total_rows;
     }
     const int k = blockIdx.x * 4 + (tid >> 6);
     if (k >= urows) return;
@@ -89,13 +93,16 @@ xbwd_pack_kernel(const typename E::src_t* __restrict__ U, void* ux, float* us, i
     float sc = 1.0f;
     if constexpr (CK == 8) {
         unsigned m = 0;
-        if (k < H)
+        if (k < H) {
+#pragma unroll 8
             for (int c = lane; c < 4 * H; c += 64) m = max(m, __float_as_uint((float)row[c]) & 0x7fffffffu);
+        }
         for (int o = 32; o > 0; o >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, o));
         if (m > 0u && __uint_as_float(m) < 3.0e38f)
             sc = __uint_as_float((unsigned)(127 + min(140 - (int)(m >> 23), 126)) << 23);
         if (lane == 0 && k < H) us[k] = __builtin_amdgcn_rcpf(sc);  // a power of two: exact
     }
+#pragma unroll 2
     for (int c = lane; c < kpad / CK; c += 64) {
         chunk_t v;
 #pragma unroll
@@ -109,14 +116,15 @@ xbwd_pack_kernel(const typename E::src_t* __restrict__ U, void* ux, float* us, i
 }
 
 hipError_t launch_xbwd_pack(const Dims& d, const XBwdConfig& xb, const void* U, void* ux, float* us,
-                            unsigned* bar, unsigned* amax, hipStream_t s) {
+                            unsigned* bar, unsigned* amax, const Meta* meta, int32_t* host_rows,
+                            hipStream_t s) {
     const dim3 grid((unsigned)((xb.urows + 3) / 4));
     if (d.bf16)
         hipLaunchKernelGGL(xbwd_pack_kernel<EltH16>, grid, dim3(256), 0, s, static_cast<const __bf16*>(U), ux, us,
-                           d.H, xb.urows, xb.kpad, bar, amax);
+                           d.H, xb.urows, xb.kpad, bar, amax, meta, host_rows);
     else
         hipLaunchKernelGGL(xbwd_pack_kernel<EltF32>, grid, dim3(256), 0, s, static_cast<const float*>(U), ux, us,
-                           d.H, xb.urows, xb.kpad, bar, amax);
+                           d.H, xb.urows, xb.kpad, bar, amax, meta, host_rows);
     return hipGetLastError();
 }
 
