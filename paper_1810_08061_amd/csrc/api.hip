@@ -115,7 +115,7 @@ struct lstm_dyn {
     TrainWs* train;            // null until the first forward for training
     int saved;                 // 1: the workspace holds a forward for training not yet used
     unsigned long long timeout_ticks;
-    int inproj_grid;
+    int inproj_grid;           // bf16 data
     long long launches_last;
     hipStream_t last_stream;   // the stream of the last forward or backward
     int has_work;              // 1 once work has been enqueued on last_stream
@@ -477,9 +477,6 @@ extern "C" int lstm_dyn_create_cell(lstm_dyn_t** out, int B, int D, int H, int T
         }
         const long long tiles = inproj_bf16_tiles_max(h->dims);
         h->inproj_grid = (int)(tiles < cus ? tiles : cus);
-    } else {
-        const long long tiles = ((long long)B * T + 127) / 128 * ((4LL * H + 127) / 128);
-        h->inproj_grid = (int)(tiles < 4LL * cus ? tiles : 4LL * cus);
     }
     h->launches_last = 0;
     h->last_stream = nullptr;
@@ -574,7 +571,7 @@ static hipError_t input_projection(lstm_dyn* h, const void* x, const void* W, co
         h->launches_last++;
         e = launch_inproj_bf16(h->dims, x, b, h->ws, h->inproj_grid, s);
     } else {
-        e = launch_inproj(h->dims, x, W, b, h->ws, h->inproj_grid, s);
+        e = launch_inproj(h->dims, x, W, b, h->ws, h->num_cus, s);
     }
     h->launches_last++;
     return e;

@@ -19,6 +19,7 @@ namespace ldyn {
 constexpr int G_THREADS = 256;
 constexpr int G_CM = 128;  // c' per tile (MFMA M)
 constexpr int G_RN = 128;  // rows per tile (MFMA N)
+constexpr int G_SMALL = 64;  // c' and rows per small tile
 
 enum GemmMode { MODE_INPROJ = 0, MODE_STEP = 1 };
 
@@ -33,42 +34,43 @@ struct GemmParams {
     const int32_t* offsets;
     int K, lda, H, t;
     int a_vec, b_vec;      // 16-byte vector loads allowed for the A rows / B rows
+    int small_below;       // small tiles where there are fewer large ones than this
 };
 
-template <typename E>
+// T: c' and rows per tile, BKB: bytes of K per block.
+template <typename E, int T, int BKB>
 struct GemmTile {
     using S = typename E::store_t;
     static constexpr int VE = 16 / sizeof(S);      // elements per 16-byte vector
-    static constexpr int BK = 64 / sizeof(S);      // K per block: 64 bytes per row
-    static constexpr int LDK = BK + VE;            // padded LDS row (80 bytes)
+    static constexpr int BK = BKB / sizeof(S);     // K per block
+    static constexpr int LDK = BK + VE;            // padded LDS row
     static constexpr int KS = BK / E::KSTEP;       // MFMA K-steps per block
-    static constexpr int UV = (G_CM / 4) / VE;     // vectors per (k, gate) row segment
+    static constexpr int UV = (T / 4) / VE;        // vectors per (k, gate) row segment
+    static constexpr int SEG = BK / VE;            // vectors per row
+    static constexpr int AV = T * SEG / G_THREADS;     // vectors per thread of either tile
+    static constexpr int FT = T / 32;              // 16 x 16 result tiles per wave and side
+    static constexpr int LDS = 2 * T * LDK;        // elements
+    static_assert(AV * G_THREADS == T * SEG && BK * 4 * UV == T * SEG, "whole vectors per thread");
 };
 
-template <typename E, int MODE>
-__global__ void __launch_bounds__(G_THREADS)
-gemm_kernel(GemmParams p) {
+// The tiles of one workgroup (grid-strided), row_base: first compact row.
+template <typename E, int MODE, int T, int BKB>
+__device__ __forceinline__ void gemm_tiles(const GemmParams& p, int nrows, int row_base,
+                                           typename E::store_t* lds) {
     using S = typename E::store_t;
     using Src = typename E::src_t;  // element type of Bw (the caller's W or U)
     static_assert(sizeof(Src) == sizeof(S), "operand and source elements have one size");
     using F = typename E::frag_t;
-    using TL = GemmTile<E>;
-    constexpr int VE = TL::VE, BK = TL::BK, LDK = TL::LDK, KS = TL::KS, UV = TL::UV;
-    __shared__ __attribute__((aligned(16))) S As[G_RN * LDK];
-    __shared__ __attribute__((aligned(16))) S Bs[G_CM * LDK];
+    using TL = GemmTile<E, T, BKB>;
+    constexpr int VE = TL::VE, BK = TL::BK, LDK = TL::LDK, KS = TL::KS, UV = TL::UV, AV = TL::AV, FT = TL::FT;
+    S* const As = lds;
+    S* const Bs = lds + T * LDK;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int H = p.H, N4 = 4 * H, K = p.K;
-    int nrows, row_base = 0;
-    if (MODE == MODE_INPROJ) {
-        nrows = p.meta->total_rows;
-    } else {
-        row_base = p.offsets[p.t];
-        nrows = p.offsets[p.t + 1] - row_base;
-    }
-    const int ntc = (N4 + G_CM - 1) / G_CM;
-    const int ntr = (nrows + G_RN - 1) / G_RN;
+    const int ntc = (N4 + T - 1) / T;
+    const int ntr = (nrows + T - 1) / T;
     const int ntiles = ntc * ntr;
     const S* __restrict__ A = static_cast<const S*>(p.A);
     const Src* __restrict__ Bw = static_cast<const Src*>(p.Bw);
@@ -76,17 +78,17 @@ gemm_kernel(GemmParams p) {
 
     for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
         const int tr = tile / ntc, tc = tile - tr * ntc;
-        const int r0 = tr * G_RN, c0 = tc * G_CM, ubase = c0 >> 2;
+        const int r0 = tr * T, c0 = tc * T, ubase = c0 >> 2;
 
-        // Per-thread source rows of the A tile (two 16-byte vectors per thread).
-        const S* arow[2];
-        bool arow_ok[2];
-        int aseg[2], ar[2];
+        // Per-thread source rows of the A tile (AV 16-byte vectors per thread).
+        const S* arow[AV];
+        bool arow_ok[AV];
+        int aseg[AV], ar[AV];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < AV; ++j) {
             const int v = tid + G_THREADS * j;
-            ar[j] = v >> 2;
-            aseg[j] = v & 3;
+            ar[j] = v / TL::SEG;
+            aseg[j] = v % TL::SEG;
             const int r = r0 + ar[j];
             arow_ok[j] = r < nrows;
             long src = 0;
@@ -94,20 +96,20 @@ gemm_kernel(GemmParams p) {
             arow[j] = A + src * p.lda;
         }
         // B tile vectors: (kk, gate, seg) per thread.
-        int bkk[2], bg[2], bseg[2];
+        int bkk[AV], bg[AV], bseg[AV];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < AV; ++j) {
             const int v = tid + G_THREADS * j;
             bseg[j] = v % UV;
             bg[j] = (v / UV) & 3;
             bkk[j] = v / (UV * 4);
         }
 
-        S areg[2][VE];
-        Src breg[2][VE];
+        S areg[AV][VE];
+        Src breg[AV][VE];
         auto load_tiles = [&](int k0) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < AV; ++j) {
                 const int k = k0 + aseg[j] * VE;
                 if (arow_ok[j] && p.a_vec && k + VE <= K) {
                     const uint4 v = *reinterpret_cast<const uint4*>(arow[j] + k);
@@ -136,7 +138,7 @@ gemm_kernel(GemmParams p) {
         };
         auto store_tiles = [&]() {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
+            for (int j = 0; j < AV; ++j) {
                 S* dst = As + ar[j] * LDK + aseg[j] * VE;
 #pragma unroll
                 for (int e = 0; e < VE; ++e) dst[e] = areg[j][e];
@@ -146,11 +148,11 @@ gemm_kernel(GemmParams p) {
             }
         };
 
-        f32x4_t acc[4][4];
+        f32x4_t acc[FT][FT];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < FT; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < FT; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
         load_tiles(0);
         __syncthreads();  // previous tile's readers are done with LDS
@@ -161,17 +163,17 @@ gemm_kernel(GemmParams p) {
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 const int koff = ks * E::KSTEP + (lane >> 4) * E::KPL;
-                F af[4], bf[4];
+                F af[FT], bf[FT];
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    af[i] = E::load(Bs + (wm * 64 + i * 16 + (lane & 15)) * LDK + koff);
+                for (int i = 0; i < FT; ++i)
+                    af[i] = E::load(Bs + (wm * (T / 2) + i * 16 + (lane & 15)) * LDK + koff);
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    bf[j] = E::load(As + (wn * 64 + j * 16 + (lane & 15)) * LDK + koff);
+                for (int j = 0; j < FT; ++j)
+                    bf[j] = E::load(As + (wn * (T / 2) + j * 16 + (lane & 15)) * LDK + koff);
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < FT; ++i)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] = E::mfma(af[i], bf[j], acc[i][j]);
+                    for (int j = 0; j < FT; ++j) acc[i][j] = E::mfma(af[i], bf[j], acc[i][j]);
             }
             __syncthreads();
             if (kb + 1 < nkb) {
@@ -182,13 +184,13 @@ gemm_kernel(GemmParams p) {
 
         // Epilogue: lane holds gates 0..3 of unit u for one row.
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int cp = c0 + wm * 64 + i * 16 + 4 * (lane >> 4);
+        for (int i = 0; i < FT; ++i) {
+            const int cp = c0 + wm * (T / 2) + i * 16 + 4 * (lane >> 4);
             const int u = cp >> 2;
             if (u >= H) continue;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int r = r0 + wn * 64 + j * 16 + (lane & 15);
+            for (int j = 0; j < FT; ++j) {
+                const int r = r0 + wn * (T / 2) + j * 16 + (lane & 15);
                 if (r >= nrows) continue;
                 f32x4_t v = acc[i][j];
                 if (MODE == MODE_INPROJ) {
@@ -205,10 +207,34 @@ gemm_kernel(GemmParams p) {
     }
 }
 
+// Input projection: tiles of 128 x 128 x 128 bytes of K (with 64 bytes 768 tiles
+// took 100 us at D 256, with 128 85: a memory latency per block of K is in the
+// way), or where those are too few to occupy the CUs (the number of rows is
+// known here only), of 64 x 64 x 256 bytes: four times as many, with half the
+// latencies in a row each.  Which: see launch_inproj.
+template <typename E, int MODE>
+__global__ void __launch_bounds__(G_THREADS)
+gemm_kernel(GemmParams p) {
+    using S = typename E::store_t;
+    using Large = GemmTile<E, G_CM, 128>;
+    using Small = GemmTile<E, G_SMALL, 256>;
+    constexpr int LDS = MODE == MODE_INPROJ && Small::LDS > Large::LDS ? Small::LDS : Large::LDS;
+    __shared__ __attribute__((aligned(16))) S lds[LDS];
+    if constexpr (MODE == MODE_INPROJ) {
+        const int nrows = p.meta->total_rows;
+        const int large = ((4 * p.H + G_CM - 1) / G_CM) * ((nrows + G_RN - 1) / G_RN);
+        if (large < p.small_below) gemm_tiles<E, MODE, G_SMALL, 256>(p, nrows, 0, lds);
+        else gemm_tiles<E, MODE, G_CM, 128>(p, nrows, 0, lds);
+    } else {
+        const int row_base = p.offsets[p.t];
+        gemm_tiles<E, MODE, G_CM, 64>(p, p.offsets[p.t + 1] - row_base, row_base, lds);
+    }
+}
+
 static bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 hipError_t launch_inproj(const Dims& d, const void* x, const void* W, const float* b,
-                         const Workspace& ws, int grid, hipStream_t s) {
+                         const Workspace& ws, int num_cus, hipStream_t s) {
     GemmParams p{};
     p.A = x;
     p.Bw = W;
@@ -219,13 +245,16 @@ hipError_t launch_inproj(const Dims& d, const void* x, const void* W, const floa
     p.K = d.D;
     p.lda = d.D;
     p.H = d.H;
-    const int ve = d.bf16 ? 8 : 4;
-    p.a_vec = (d.D % ve == 0) && aligned16(x);
-    p.b_vec = (d.H % ve == 0) && aligned16(W);
-    if (d.bf16)
-        hipLaunchKernelGGL((gemm_kernel<EltBF16, MODE_INPROJ>), dim3(grid), dim3(G_THREADS), 0, s, p);
-    else
-        hipLaunchKernelGGL((gemm_kernel<EltF32, MODE_INPROJ>), dim3(grid), dim3(G_THREADS), 0, s, p);
+    p.a_vec = (d.D % 4 == 0) && aligned16(x);
+    p.b_vec = (d.H % 4 == 0) && aligned16(W);
+    // Small tiles while there is less than one large tile per CU: 64 and 128
+    // large ones take 37 and 38 us at D 256 (61 and 62 at D 512), their four
+    // times as many small ones 18 and 24 (25 and 36); 256 the same either way;
+    // 512 take 56 us and 66.
+    p.small_below = num_cus;
+    const long long tiles = (((long long)d.B * d.T + G_SMALL - 1) / G_SMALL) * ((4LL * d.H + G_SMALL - 1) / G_SMALL);
+    const int grid = (int)(tiles < 4LL * num_cus ? tiles : 4LL * num_cus);
+    hipLaunchKernelGGL((gemm_kernel<EltF32, MODE_INPROJ>), dim3(grid), dim3(G_THREADS), 0, s, p);
     return hipGetLastError();
 }
 

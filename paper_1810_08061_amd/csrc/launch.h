@@ -62,8 +62,9 @@ long long carve_forward_workspace(const Dims& d, char* base, Workspace* ws, long
                                   long long* hx_bytes, long long ux_bytes);
 
 // Input projection over all valid (b, t): gx[r][c'] = x[rowsrc[r]] . W[:, col(c')] + b[col(c')].
+// (fp32 data)
 hipError_t launch_inproj(const Dims& d, const void* x, const void* W, const float* b,
-                         const Workspace& ws, int grid, hipStream_t s);
+                         const Workspace& ws, int num_cus, hipStream_t s);
 
 // bf16 input projection: W -> Wt, then the tiled GEMM (inproj.hip).
 void inproj_bf16_wt_shape(const Dims& d, int* np, int* dp);

@@ -150,8 +150,7 @@ extern "C" int lstm_dyn_forward_noalloc(int B, int D, int H, int T, int dtype, c
             NA_CHECK(launch_transpose_w(d, W, ws, s));
             NA_CHECK(launch_inproj_bf16(d, x, b, ws, (int)(tiles < ds.num_cus ? tiles : ds.num_cus), s));
         } else {
-            const long long tiles = ((long long)B * T + 127) / 128 * ((4LL * H + 127) / 128);
-            NA_CHECK(launch_inproj(d, x, W, b, ws, (int)(tiles < 4LL * ds.num_cus ? tiles : 4LL * ds.num_cus), s));
+            NA_CHECK(launch_inproj(d, x, W, b, ws, ds.num_cus, s));
         }
         PersistentConfig pc{plan.mt, plan.groups, plan.ksw, plan.kw, plan.nstate, plan.lds_bytes,
                             timeout_ticks, nullptr, nullptr, nullptr};
