@@ -44,35 +44,46 @@ seq_finish_kernel(SeqParams p) {
 
 // Output sequence of the forward for training: the state after step t of a
 // row is the state step t + 1 started from (kept per compact row), or its
-// final state after its last step.  Zeros past each length.
+// final state after its last step.  Zeros past each length.  One wave per
+// output row, bound by its writes (26 MB at 128 rows, 100 steps, H = 512: 20 us
+// with one element per thread and three divisions for it, 9 us so); VEC: four
+// elements per access (H a multiple of 4, out_h and seq 16-byte aligned).
+template <bool VEC>
 __global__ void __launch_bounds__(256)
 seq_from_saved_kernel(float* seq, const float* __restrict__ save_h, const float* __restrict__ out_h,
                       const int32_t* __restrict__ perm, const int32_t* __restrict__ offsets,
                       const int32_t* __restrict__ lengths, int B, int T, int H) {
-    // one slot s per workgroup row; slot order is the length order
-    const long n = (long)B * T * H;
-    for (long i = blockIdx.x * 256L + threadIdx.x; i < n; i += (long)gridDim.x * 256) {
-        const long bt = i / H;
-        const int u = (int)(i - bt * H);
-        const int s = (int)(bt / T), t = (int)(bt - (long)s * T);
+    constexpr int V = VEC ? 4 : 1;
+    typedef float v_t __attribute__((ext_vector_type(V)));
+    const int lane = threadIdx.x & 63;
+    const long n = (long)B * T;
+    // rows in slot order, which is the length order: neighbours read neighbours
+    for (long q = blockIdx.x * 4L + (threadIdx.x >> 6); q < n; q += gridDim.x * 4L) {
+        const int s = (int)(q / T), t = (int)(q - (long)s * T);
         const int b = perm[s];
         const int L = min(max(lengths[b], 0), T);
-        float v = 0.0f;
-        if (t + 1 < L) v = save_h[(long)(offsets[t + 1] + s) * H + u];
-        else if (t + 1 == L) v = out_h[(long)b * H + u];
-        seq[((long)b * T + t) * H + u] = v;
+        v_t* dst = reinterpret_cast<v_t*>(seq + ((long)b * T + t) * H);
+        if (t < L) {
+            const v_t* src = reinterpret_cast<const v_t*>(t + 1 < L ? save_h + (long)(offsets[t + 1] + s) * H
+                                                                    : out_h + (long)b * H);
+#pragma unroll 4
+            for (int u = lane; u < H / V; u += 64) dst[u] = src[u];
+        } else {
+            for (int u = lane; u < H / V; u += 64) dst[u] = v_t{};
+        }
     }
 }
 
 hipError_t launch_seq_from_saved(const Dims& d, float* seq, const float* save_h, const float* out_h,
                                  const int32_t* lengths, const Workspace& ws, int num_cus,
                                  hipStream_t s) {
-    const long n = (long)d.B * d.T * d.H;
-    long grid = (n + 255) / 256;
+    long grid = ((long)d.B * d.T + 3) / 4;
     if (grid > 16L * num_cus) grid = 16L * num_cus;
-    if (grid < 1) grid = 1;
-    hipLaunchKernelGGL(seq_from_saved_kernel, dim3((unsigned)grid), dim3(256), 0, s, seq, save_h,
-                       out_h, ws.perm, ws.offsets, lengths, d.B, d.T, d.H);
+    const bool vec =
+        d.H % 4 == 0 && ((reinterpret_cast<uintptr_t>(seq) | reinterpret_cast<uintptr_t>(out_h)) & 15) == 0;
+    auto k = vec ? seq_from_saved_kernel<true> : seq_from_saved_kernel<false>;
+    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(256), 0, s, seq, save_h, out_h, ws.perm, ws.offsets,
+                       lengths, d.B, d.T, d.H);
     return hipGetLastError();
 }
 
