@@ -106,4 +106,26 @@ __device__ inline int kslot(int ks, int l) {
 // stay in flight.
 __device__ inline void x_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// Products of at most four rows, fp32.  MFMA 4x4x1 forms sixteen 4 x 4 blocks at
+// once, block l >> 2 of lane l; with the fragments of a 16x16x4 MFMA (lane l:
+// column l & 15 of U, k run l >> 4) and row l & 3 of h in lane l, block 4 q + c is
+// columns 4 c .. 4 c + 3 of run q.  It takes 8 cycles where 16x16x4, four fifths
+// of it for rows that are not there, takes 32.  sum_runs adds the four runs.
+__device__ inline f32x4_t mfma_few(float a, float b, f32x4_t c) {
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0);
+}
+__device__ inline f32x4_t sum_runs(f32x4_t v) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        // swapping a value's halves (then odd and even quarters) with itself
+        // leaves one copy of each beside the other in every lane
+        unsigned x = __float_as_uint(v[e]);
+        const auto h = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        x = __float_as_uint(__uint_as_float(h[0]) + __uint_as_float(h[1]));
+        const auto q = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        v[e] = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+    }
+    return v;
+}
+
 }  // namespace ldyn

@@ -284,13 +284,14 @@ xbwd_kernel(XBwdParams p) {
     auto leaves = [&](int at) __attribute__((always_inline)) {
         return __builtin_amdgcn_readfirstlane(seen_abort) <= at;
     };
+    const bool few = F32 && RG <= 4;  // products of four rows (loop.h), by the batch as in xloop_kernel.h
     // Row tile j: the wave's part of dh_t into LDS; false where the loop ended
     // at the last barrier.
     auto product_tile = [&](int j, int rows) __attribute__((always_inline)) -> bool {
         // (lanes without a row take the tile's first: its products are not used,
         // and no row of another tile may stand in, whose slot may be marked
         // again while this tile is still read)
-        const int r = j * 16 + (l & 15), rr = r < rows ? r : j * 16;
+        const int r = j * 16 + (l & (few ? 3 : 15)), rr = r < rows ? r : j * 16;
         const unsigned slot = turn & 3u;
         const unsigned lane = slot * ring + (unsigned)kb0 * blk_bytes + (unsigned)((l >> 4) * RG + rr) * 16u;
         const unsigned slane = slot * sring + (unsigned)(rr * NBLK + kb0) * 2u;
@@ -375,9 +376,15 @@ xbwd_kernel(XBwdParams p) {
                 } while (incomplete(c));
             }
             if constexpr (F32) {
+                if (few) {
 #pragma unroll
-                for (int k = 0; k < 4 * NBC; ++k)
-                    acc[k & 3] = E::mfma(afrag[0][c * 4 * NBC + k], __uint_as_float(f[c % NBUF][k >> 2][k & 3]), acc[k & 3]);
+                    for (int k = 0; k < 4 * NBC; ++k)
+                        acc[k & 3] = mfma_few(afrag[0][c * 4 * NBC + k], __uint_as_float(f[c % NBUF][k >> 2][k & 3]), acc[k & 3]);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 4 * NBC; ++k)
+                        acc[k & 3] = E::mfma(afrag[0][c * 4 * NBC + k], __uint_as_float(f[c % NBUF][k >> 2][k & 3]), acc[k & 3]);
+                }
             } else {
 #pragma unroll
                 for (int b = 0; b < NBC; ++b) {
@@ -395,8 +402,15 @@ xbwd_kernel(XBwdParams p) {
             }
             if (c + NBUF < NCH) load_chunk(c + NBUF);
         }
-        if constexpr (F32) acc[0] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
         float* const part = lds + (cnt & 1) * (LY::PART / 4);
+        if constexpr (F32) {
+            acc[0] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+            if (few) {  // lane l: row l & 3, units 4 (l >> 2) ..; to their place below
+                acc[0] = sum_runs(acc[0]);
+                if (l < 16) *reinterpret_cast<f32x4_t*>(part + ((w * 64 + (l >> 2) * 16 + (l & 3)) << 2)) = acc[0];
+                return true;
+            }
+        }
 #pragma unroll
         for (int mt = 0; mt < MTU; ++mt)
             *reinterpret_cast<f32x4_t*>(part + (((w * MTU + mt) * 64 + l) << 2)) = acc[mt];

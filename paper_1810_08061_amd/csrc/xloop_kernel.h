@@ -403,6 +403,12 @@ xloop_kernel(XLoopParams p) {
         if constexpr (STOP) out |= __builtin_amdgcn_readfirstlane(seen_run) == 0;
         return out;
     };
+    // fp32, at most four rows per group: products of four rows (loop.h).  By the
+    // batch, not by the rows that still run, so that every row of a batch goes
+    // the same way whatever its slot.  (32 rows, H 256, 100 steps: a forward 172 ->
+    // 164 us; with the reverse loop's a training step 497 -> 398, RNN H 333 364 ->
+    // 295.)
+    const bool few = E::KPL == 1 && RG <= 4;
     // Loads the wave's part of tile j and polls it; false where the loop ended
     // at the last barrier (known only here, so that the loads travel while the
     // flags are read).
@@ -410,7 +416,7 @@ xloop_kernel(XLoopParams p) {
         // lanes without an active row read the tile's first row instead, whose
         // products they then repeat (no row of another tile may stand in, whose
         // slot other workgroups may mark again while this tile is still read)
-        const int r = j * 16 + (l & 15);
+        const int r = j * 16 + (l & (few ? 3 : 15));
         const unsigned lane = (unsigned)(t & 3) * ring + (unsigned)(kw0 / KB) * blk_bytes +
                               (unsigned)((l >> 4) * RG + (r < rows ? r : j * 16)) * 16u;
         stress_delay(t, 1 + j);
@@ -452,6 +458,36 @@ xloop_kernel(XLoopParams p) {
         return true;
     };
     auto mma_tile = [&]() __attribute__((always_inline)) {
+        float* const part = lds + (cnt & 1) * (LY::PART / 4);
+        if constexpr (E::KPL == 1) {
+            if (few) {
+                constexpr int NC = MT == 1 ? 4 : 2;  // chains per gate tile: an MFMA does not wait for the last
+                f32x4_t acc[MT][NC];
+                f32x4_t sacc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) acc[mt][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int ks = 0; ks < KSW; ++ks) {
+                    const float b = __uint_as_float(f[ks >> 2][ks & 3]);
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) acc[mt][ks % NC] = mfma_few(afrag[mt][ks], b, acc[mt][ks % NC]);
+                    if constexpr (STOP) sacc = E::mfma(E::load(vst + kw0 + kslot<E, KSW>(ks, l)), b, sacc);
+                }
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    f32x4_t v = acc[mt][0] + acc[mt][1];
+                    if constexpr (NC == 4) v += acc[mt][2] + acc[mt][3];
+                    v = sum_runs(v);  // lane l: row l & 3, unit l >> 2; to the place of (row, unit) below
+                    if (l < 16) *reinterpret_cast<f32x4_t*>(part + (((w * MT + mt) * 64 + (l >> 2) * 16 + (l & 3)) << 2)) = v;
+                }
+                if constexpr (STOP) {
+                    if (l < 16) s_part[cnt & 1][w][l] = sacc[0];
+                }
+                return;
+            }
+        }
         f32x4_t acc[MT];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -467,7 +503,6 @@ xloop_kernel(XLoopParams p) {
             // this wave's partial v . h of row (l & 15) of the tile
             if constexpr (STOP) sacc = E::mfma(E::load(vst + kw0 + kslot<E, KSW>(ks, l)), b, sacc);
         }
-        float* const part = lds + (cnt & 1) * (LY::PART / 4);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
             *reinterpret_cast<f32x4_t*>(part + (((w * MT + mt) * 64 + l) << 2)) = acc[mt];
