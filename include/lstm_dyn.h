@@ -56,9 +56,9 @@ enum { LSTM_DYN_F32 = 0, LSTM_DYN_BF16 = 1 };
  * PERSISTENT: the time loop runs on the device inside one persistent kernel
  *   (one grid barrier at its start, then each step waits only for the hidden
  *   state it reads; loop bound and early exit read on the device).  Launches
- *   per forward: length preparation (with it the layouts of W and U that the
- *   others read), input projection, the loop; one more for the GRU and RNN
- *   cells (their weights are repacked); a single launch when the
+ *   per forward: length preparation, input projection (two launches with
+ *   bf16 data: a transpose of W, then the GEMM), the loop; one more for the
+ *   GRU and RNN cells (their weights are repacked); a single launch when the
  *   hidden width is at most 32 and the whole forward fits one workgroup.
  *   None of them waits for the host.
  * PER_STEP: the comparison path of the paper's eager-vs-graph experiment
@@ -100,9 +100,7 @@ enum {
     LSTM_DYN_Q_LAST_STATUS = 0,        /* status of the last forward (synchronises its stream) */
     LSTM_DYN_Q_STEPS_EXECUTED = 1,     /* loop iterations of the last forward = max_b L[b] (synchronises) */
     LSTM_DYN_Q_LAUNCHES_PER_FORWARD = 2, /* kernel launches issued by the last forward */
-    LSTM_DYN_Q_GROUPS = 3,             /* workgroups of the device-wide persistent kernel (lstm_dyn_plan);
-                                          where all of U fits one XCD's CUs the loop runs as one group
-                                          of workgroups per XCD instead */
+    LSTM_DYN_Q_GROUPS = 3,             /* workgroups of the persistent kernel */
     LSTM_DYN_Q_WORKSPACE_BYTES = 4,    /* device workspace owned by the handle */
     LSTM_DYN_Q_TOTAL_ROWS = 5,         /* sum of the (clamped) lengths of the last forward (synchronises) */
     LSTM_DYN_Q_TIME_PREP_NS = 6,       /* with LSTM_DYN_OPT_TIMING: device time of the length
@@ -264,8 +262,8 @@ int lstm_dyn_forward_train(lstm_dyn_t* h, const void* x, const int32_t* lengths,
  * valid steps) are products with fp32 accumulation, of fp32 operands with
  * fp32 data and of fp16 operands with bf16 data (each scaled by a power of
  * two: U per row or as a whole, the weight-gradient operands as a whole, dz
- * per row or per row and 32-column block).  Waits once for the host's copy of
- * the sum of lengths (and, where the host issues the steps, their offsets).  The reverse
+ * per row or per row and 32-column block).  Waits once or twice for copies to
+ * the host (the sum of lengths, the operands' largest magnitudes).  The reverse
  * loop of a persistent handle is one cooperative launch where U fits the CUs of
  * one XCD (B <= 256 on a 256-CU device; bf16 data: H < 1024, fp32 data: H <=
  * 512) and, with bf16 data, where H is a multiple of 256 (H <= 2048, B <=
@@ -301,12 +299,10 @@ int lstm_dyn_set_option(lstm_dyn_t* h, int option, long long value);
  * the wait for the other workgroups) -- then the loop end) into
  * ticks[0 .. capacity), synchronising the forward's stream; *count receives
  * the number of entries and *khz the clock rate.  A backward pass run as
- * one launch of the whole reverse loop records there instead; the one in column
- * blocks (bf16 data, persistent handle, H a multiple of 256 beyond 512), at 4 t for step t: its start, its
+ * one launch of the whole reverse loop (bf16 data, persistent handle, H a
+ * multiple of 256) records there instead, at 4 t for step t: its start, its
  * share of dh published, its cells done (the other shares awaited), the
- * marks for later steps issued; at 4 max_len the product for dh0.  The one in a
- * group of workgroups per XCD: its start, its first row tile's product done, its
- * last tile's cells done, the step's end.
+ * marks for later steps issued; at 4 max_len the product for dh0.
  * Returns LSTM_DYN_OK, ERR_INVALID (option not set, NULL arguments) or ERR_HIP.
  */
 int lstm_dyn_step_trace(lstm_dyn_t* h, long long* ticks, int capacity, int* count, int* khz);

@@ -567,6 +567,8 @@ static hipError_t input_projection(lstm_dyn* h, const void* x, const void* W, co
                                    hipStream_t s) {
     hipError_t e;
     if (h->dims.bf16) {
+        if ((e = launch_transpose_w(h->dims, W, h->ws, s)) != hipSuccess) return e;
+        h->launches_last++;
         e = launch_inproj_bf16(h->dims, x, b, h->ws, h->inproj_grid, s);
     } else {
         e = launch_inproj(h->dims, x, W, b, h->ws, h->num_cus, s);
@@ -621,7 +623,7 @@ static int forward_impl(lstm_dyn_t* h, const void* x, const int32_t* lengths, co
         }
         return LSTM_DYN_OK;
     }
-    LD_CHECK(launch_prep(d, lengths, h->ws, s, stop != nullptr, W, U, &h->xl[stop ? 1 : 0]));
+    LD_CHECK(launch_prep(d, lengths, h->ws, s, stop != nullptr, U, &h->xl[stop ? 1 : 0]));
     h->launches_last += 1 + pack_launches;
     LD_CHECK(mark(1));
     if (h->mode == LSTM_DYN_PERSISTENT) {
@@ -913,7 +915,7 @@ extern "C" int lstm_dyn_forward_train(lstm_dyn_t* h, const void* x, const int32_
         b = h->b4;
         h->launches_last++;
     }
-    LD_CHECK(launch_prep(d, lengths, h->ws, s, false, W, U, &h->xl[2]));
+    LD_CHECK(launch_prep(d, lengths, h->ws, s, false, U, &h->xl[2]));
     LD_CHECK(mark(1));
     h->launches_last++;
     if (h->mode == LSTM_DYN_PERSISTENT && !h->plan.single && h->save_ok) {

@@ -47,14 +47,13 @@ hipError_t launch_cell_pack(const Dims& d, const void* W, const void* U, const f
 // per-step active counts and compact row offsets, compact row sources.
 // stop: rows may end before their lengths, so the steps that some row ran
 // (meta->iters) start at zero for the loop to count.
-// With W and bf16 data, further workgroups of the launch write ws.wt for the
-// input projection (inproj_bf16_wt_shape).  With U and ws.ux, further workgroups of the launch write U for the
+// With U and ws.ux, further workgroups of the launch write U for the
 // XCD-grouped loop: 1 KB blocks, block (ug, kb) the MFMA A-fragment of units
 // 4 ug .. 4 ug + 3 (16 gate-interleaved columns) and one run of k (32 in fp16,
 // 16 in fp32), zero past H; xc gives the padded sizes.
 struct XLoopConfig;
 hipError_t launch_prep(const Dims& d, const int32_t* lengths, const Workspace& ws, hipStream_t s,
-                       bool stop, const void* W, const void* U, const XLoopConfig* xc);
+                       bool stop = false, const void* U = nullptr, const XLoopConfig* xc = nullptr);
 
 // The workspace of a persistent-mode LSTM forward carved from caller memory
 // (api.hip): returns its bytes; fills ws when base is not null.
@@ -67,10 +66,11 @@ long long carve_forward_workspace(const Dims& d, char* base, Workspace* ws, long
 hipError_t launch_inproj(const Dims& d, const void* x, const void* W, const float* b,
                          const Workspace& ws, int num_cus, hipStream_t s);
 
-// bf16 input projection: the tiled GEMM on Wt (inproj.hip).
+// bf16 input projection: W -> Wt, then the tiled GEMM (inproj.hip).
 void inproj_bf16_wt_shape(const Dims& d, int* np, int* dp);
 int inproj_bf16_tiles_max(const Dims& d);
 hipError_t inproj_bf16_setup();
+hipError_t launch_transpose_w(const Dims& d, const void* W, const Workspace& ws, hipStream_t s);
 hipError_t launch_inproj_bf16(const Dims& d, const void* x, const float* b, const Workspace& ws,
                               int grid, hipStream_t s);
 

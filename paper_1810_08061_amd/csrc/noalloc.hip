@@ -143,10 +143,11 @@ extern "C" int lstm_dyn_forward_noalloc(int B, int D, int H, int T, int dtype, c
                                reinterpret_cast<uint4*>(ds.ptr + hx_off), n16);
             NA_CHECK(hipGetLastError());
         }
-        NA_CHECK(launch_prep(d, lengths, ws, s, false, W, U, &xc));
+        NA_CHECK(launch_prep(d, lengths, ws, s, false, U, &xc));
         if (bf16) {
             NA_CHECK(inproj_bf16_setup());
             const long long tiles = inproj_bf16_tiles_max(d);
+            NA_CHECK(launch_transpose_w(d, W, ws, s));
             NA_CHECK(launch_inproj_bf16(d, x, b, ws, (int)(tiles < ds.num_cus ? tiles : ds.num_cus), s));
         } else {
             NA_CHECK(launch_inproj(d, x, W, b, ws, ds.num_cus, s));

@@ -1,5 +1,4 @@
-// prep.hip -- loop bound, length sort and compact row tables, on the device;
-// beside them, in other workgroups, the weights' layouts.
+// prep.hip -- loop bound, length sort and compact row tables, on the device.
 //
 // The paper's loop bound is the maximum sequence length (Section 9 "RNN
 // cells"; Appendix A); here it is reduced on the device so no host round trip
@@ -25,7 +24,6 @@ struct PackUParams {
     const void* U;
     void* ux;
     int H, hpad, ugroups, bf16;
-    int blocks;  // workgroups, from 1 on
 };
 
 template <typename E>
@@ -39,7 +37,7 @@ __device__ inline void pack_u_tiles(const PackUParams& q, void* lds) {
     const Src* U = static_cast<const Src*>(q.U);
     const int H = q.H, tid = threadIdx.x, nkt = q.hpad / 64, nut = (q.ugroups + 3) / 4;
     const size_t H4 = 4 * (size_t)H;
-    for (int it = blockIdx.x - 1; it < nkt * nut; it += q.blocks) {
+    for (int it = blockIdx.x - 1; it < nkt * nut; it += gridDim.x - 1) {
         const int k0 = it % nkt * 64, u0 = it / nkt * 16;
         {
             const int quad = tid & 3, gate = (tid >> 2) & 3, kl = tid >> 4;
@@ -66,67 +64,15 @@ __device__ inline void pack_u_tiles(const PackUParams& q, void* lds) {
         }
     }
 }
-// bf16 data: Wt[c'][k] = W[k][col(c')] for c' < 4H, k < D; zero elsewhere (np x
-// dp), for the input projection.  A tile is 128 k by 64 c'; its 64 c' are 16 units
-// times the four gates, so in a row of W they are four runs of 16 consecutive
-// columns.  Each thread reads one 16-byte piece of those runs (element by
-// element when H is not a multiple of 8 or at the edges of W), the tile turns
-// through LDS, and 16-byte pieces of k leave it for rows of Wt (dp is a
-// multiple of 64).  Beside the length sort it costs no time of its own; as a
-// launch it took 4.7 us (512 x 2048) to 14 (1024 x 8192), and the gap before it.
-struct WtParams {
-    const __bf16* W;
-    __bf16* Wt;  // null: none
-    int D, H, np, dp;
-    int first;   // first workgroup
-};
-
-constexpr int WT_K = 128, WT_LDT = WT_K + 8;  // k per tile, and bf16 per LDS row
-
-__device__ inline void transpose_w_tiles(const WtParams& q, void* lds) {
-    __bf16* const tile = static_cast<__bf16*>(lds);  // [64 c'][WT_LDT]
-    const int D = q.D, H = q.H, tid = threadIdx.x;
-    const int nkt = (q.dp + WT_K - 1) / WT_K, tiles = nkt * (q.np / 64);
-    const size_t H4 = 4 * (size_t)H;
-    const bool rows8 = (H % 8) == 0 && (reinterpret_cast<uintptr_t>(q.W) & 15) == 0;
-    for (int it = blockIdx.x - q.first; it < tiles; it += gridDim.x - q.first) {
-        const int k0 = it % nkt * WT_K, c0 = it / nkt * 64, u0 = c0 / 4;
-        const int kl = tid >> 3, g = (tid >> 1) & 3, ub = u0 + 8 * (tid & 1);  // row, gate, first unit
-        const int k = k0 + kl;
-        bf16x8_t v;
-        if (rows8 && k < D && ub + 8 <= H) {
-            v = *reinterpret_cast<const bf16x8_t*>(q.W + (size_t)k * H4 + (size_t)g * H + ub);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                v[e] = (k < D && ub + e < H) ? q.W[(size_t)k * H4 + (size_t)g * H + ub + e] : (__bf16)0.0f;
-        }
-        __syncthreads();  // the last tile has been read
-#pragma unroll
-        for (int e = 0; e < 8; ++e) tile[(4 * (ub - u0 + e) + g) * WT_LDT + kl] = v[e];
-        __syncthreads();
-        const int cl = tid >> 4, kp = 8 * (tid & 15);
-        if (k0 + kp < q.dp)
-            *reinterpret_cast<bf16x8_t*>(q.Wt + (size_t)(c0 + cl) * q.dp + k0 + kp) =
-                *reinterpret_cast<const bf16x8_t*>(tile + cl * WT_LDT + kp);
-    }
-}
-
-constexpr int WT_LDS = 64 * WT_LDT * 2;
-static_assert(PREP_THREADS == 1024, "one piece per thread");
 constexpr int PACK_LDS = 64 * (64 + 4) * 4 > 64 * (64 + 8) * 2 ? 64 * (64 + 4) * 4 : 64 * (64 + 8) * 2;
 
 __global__ void __launch_bounds__(PREP_THREADS)
 prep_kernel(const int32_t* __restrict__ lengths, int B, int T, Meta* __restrict__ meta,
             int32_t* __restrict__ perm, int32_t* __restrict__ offsets,
             int32_t* __restrict__ rowsrc, unsigned* __restrict__ bar, int iters0,
-            PackUParams pack, WtParams wt) {
+            PackUParams pack) {
     constexpr int NW = PREP_THREADS / 64;
     extern __shared__ __attribute__((aligned(16))) int32_t sh[];
-    if (wt.Wt && (int)blockIdx.x >= wt.first) {
-        transpose_w_tiles(wt, sh);
-        return;
-    }
     if (blockIdx.x > 0) {
         if (pack.bf16) pack_u_tiles<EltH16>(pack, sh);
         else pack_u_tiles<EltF32>(pack, sh);
@@ -283,27 +229,19 @@ prep_kernel(const int32_t* __restrict__ lengths, int B, int T, Meta* __restrict_
 }
 
 hipError_t launch_prep(const Dims& d, const int32_t* lengths, const Workspace& ws, hipStream_t s,
-                       bool stop, const void* W, const void* U, const XLoopConfig* xc) {
+                       bool stop, const void* U, const XLoopConfig* xc) {
     if (d.B > PREP_MAX_B) return hipErrorInvalidValue;
     size_t lds = (size_t)2 * d.B * sizeof(int32_t);
     PackUParams pack{};
     int grid = 1;
     if (U && xc && xc->variant && ws.ux) {
+        pack = PackUParams{U, ws.ux, d.H, xc->hpad, xc->ugroups, d.bf16};
         const int tiles = (xc->hpad / 64) * ((xc->ugroups + 3) / 4);
-        pack = PackUParams{U, ws.ux, d.H, xc->hpad, xc->ugroups, d.bf16, tiles < 255 ? tiles : 255};
-        grid += pack.blocks;
+        grid += tiles < 255 ? tiles : 255;
         if (lds < PACK_LDS) lds = PACK_LDS;
     }
-    WtParams wt{};
-    if (W && d.bf16) {
-        wt = WtParams{static_cast<const __bf16*>(W), static_cast<__bf16*>(ws.wt), d.D, d.H, 0, 0, grid};
-        inproj_bf16_wt_shape(d, &wt.np, &wt.dp);
-        const long long tiles = (long long)((wt.dp + WT_K - 1) / WT_K) * (wt.np / 64);
-        grid += (int)(tiles < 512 ? tiles : 512);
-        if (lds < WT_LDS) lds = WT_LDS;
-    }
     hipLaunchKernelGGL(prep_kernel, dim3(grid), dim3(PREP_THREADS), lds, s, lengths, d.B, d.T, ws.meta,
-                       ws.perm, ws.offsets, ws.rowsrc, ws.bar, stop ? 0 : -1, pack, wt);
+                       ws.perm, ws.offsets, ws.rowsrc, ws.bar, stop ? 0 : -1, pack);
     return hipGetLastError();
 }
 
