@@ -13,10 +13,20 @@
 // A step is one chain: h from LDS, the products of h (fp32: 16 of 32 cycles each
 // per SIMD), the gates, h to LDS, a barrier.  The products of x need no h: those
 // of step t + 1 are issued right after step t's products of h and run in the
-// matrix unit while the gates are computed, on x loaded two steps ahead.  Eight
-// waves of one gate tile, h U in two chains, instead of four waves of two tiles
-// with both products in the chain: 4 rows, D 16, H 32, 20 steps 25.8 -> 19.8 us a
-// call.
+// matrix unit while the gates are computed, on x loaded ahead.  Eight waves of
+// one gate tile, h U in two chains, instead of four waves of two tiles with both
+// products in the chain.
+//
+// Every wave needs all of x_t, whose fragments are gathers of single elements (D
+// is any number).  The workgroup gathers each 16-byte chunk of them once, by one
+// of its waves, and shares it through LDS.  Taken by each wave for itself, these
+// loads are what a step waits for; 64 rows, 60 steps, with four waves of two
+// tiles, with eight waves that each take all of x, and shared:
+//   fp32 D 16    340, 357 and 188 us
+//   fp32 D 64    727, 1027 and 332
+//   bf16 D 128  1020, 1704 and 313
+// (16 rows, fp32 D 12, 200 steps with the sequence: 336, 369 and 231; 4 rows, D 16,
+// 20 steps: 50.7, 44.5 and 39.4.)
 #include "launch.h"
 
 namespace ldyn {
@@ -59,6 +69,11 @@ small_kernel(SmallParams p) {
     __shared__ __attribute__((aligned(16))) SH hs[2][NT * 16 * HS];
     __shared__ int len[NT * 16];
     __shared__ int maxlen, bad;
+    // x of a step as chunks of 16 bytes per lane: CPU K-steps of one row tile each
+    constexpr int CPU = 16 / (int)sizeof(F), CHUNKS = NT * KD / CPU;
+    static_assert(KD % CPU == 0, "whole chunks");
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    __shared__ u32x4 xs[2][CHUNKS * 64];  // by step parity
     __shared__ int ended[NT * 16];  // termination from the state: 1 once the row ended
     __shared__ int ran[2];          // some row ran at step t (slot t & 1)
 
@@ -146,27 +161,42 @@ small_kernel(SmallParams p) {
     __syncthreads();
     const int ml = maxlen;
 
-    // x fragments of one step: lane holds row nt*16 + (l & 15), K slice of D.
-    // two steps ahead of their products where two sets fit the registers
-    constexpr int AHEAD = NT * KD * (int)sizeof(F) <= 128 ? 2 : 1;
-    F xa[NT][KD], xb[NT][KD];
-    auto load_x = [&](F (&dst)[NT][KD], int t) {
+    // One K-step's x fragment of a row tile: lane holds row nt*16 + (l & 15), K slice of D.
+    auto load_frag = [&](int nt, int ks, int t) __attribute__((always_inline)) -> F {
+        const int n = nt * 16 + (l & 15);
+        const size_t row = (size_t)min(n, B - 1) * T + min(t, T - 1);
+        F f = E::zero();
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const int n = nt * 16 + (l & 15);
-            const size_t row = (size_t)min(n, B - 1) * T + min(t, T - 1);
+        for (int e = 0; e < E::KPL; ++e) {
+            const int k = ks * E::KSTEP + (l >> 4) * E::KPL + e;
+            const S v = X[row * D + min(k, D - 1)];
+            if constexpr (E::KPL == 1) f = k < D ? v : 0.0f;
+            else f[e] = k < D ? v : E::from_f32(0.0f);
+        }
+        return f;
+    };
+    // The wave's chunks of a step: OWN of them.  Dealt from the last wave on where
+    // that one owns no unit (1 row, H = 8, 60 steps: 72 us from the first wave, 67
+    // from the last), else from the first, which the SIMD issues first (bf16, 1
+    // row, H = 32, 60 steps: 51.3 us from the first, 54.4 from the last).
+    constexpr int OWN = (CHUNKS + SM_WAVES - 1) / SM_WAVES;
+    F xo[OWN][CPU];
+    const int w_own = H > 4 * (SM_WAVES - 1) ? w : SM_WAVES - 1 - w;
+    auto own = [&](int i) __attribute__((always_inline)) { return w_own + i * SM_WAVES; };
+    auto load_x = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
-            for (int ks = 0; ks < KD; ++ks) {
-                F f = E::zero();
+        for (int i = 0; i < OWN; ++i) {
+            const int c = own(i);
+            if (c < CHUNKS)
 #pragma unroll
-                for (int e = 0; e < E::KPL; ++e) {
-                    const int k = ks * E::KSTEP + (l >> 4) * E::KPL + e;
-                    const S v = X[row * D + min(k, D - 1)];
-                    if constexpr (E::KPL == 1) f = k < D ? v : 0.0f;
-                    else f[e] = k < D ? v : E::from_f32(0.0f);
-                }
-                dst[nt][ks] = f;
-            }
+                for (int e = 0; e < CPU; ++e) xo[i][e] = load_frag(c / (KD / CPU), c % (KD / CPU) * CPU + e, t);
+        }
+    };
+    auto share_x = [&](int t) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) {
+            const int c = own(i);
+            if (c < CHUNKS) xs[t & 1][c * 64 + l] = __builtin_bit_cast(u32x4, xo[i]);
         }
     };
     int lenr[NT];
@@ -176,43 +206,52 @@ small_kernel(SmallParams p) {
     // x_t W + b of the step to come: its products run while the step before
     // computes its gates
     f32x4_t accx[NT];
-    auto project = [&](const F (&x)[NT][KD]) {
+    auto project = [&](int t) __attribute__((always_inline)) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) accx[nt] = bias;
 #pragma unroll
-        for (int ks = 0; ks < KD; ++ks)
+        for (int kc = 0; kc < KD / CPU; ++kc)
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) accx[nt] = E::mfma(wf[ks], x[nt][ks], accx[nt]);
+            for (int nt = 0; nt < NT; ++nt) {
+                const u32x4 v = xs[t & 1][(nt * (KD / CPU) + kc) * 64 + l];
+                F f[CPU];
+                __builtin_memcpy(f, &v, sizeof(v));
+#pragma unroll
+                for (int e = 0; e < CPU; ++e) accx[nt] = E::mfma(wf[kc * CPU + e], f[e], accx[nt]);
+            }
     };
     if (ml > 0) {
-        load_x(xa, 0);
-        if constexpr (AHEAD == 2) load_x(xb, 2);
-        project(xa);
-        load_x(xa, 1);
+        load_x(0);
+        share_x(0);
+        load_x(1);
+        share_x(1);
+        load_x(2);
+        __syncthreads();
+        project(0);
+        __syncthreads();  // x_0 has been read: step 0 puts x_2 in its place
     }
 
     int iters = 0;  // termination from the state: steps in which some row ran
     int t = 0;
-    // Step t; x holds x_{t+1} and is refilled with x_{t+1+AHEAD}.  False where
-    // the loop ends.
-    auto step = [&](F (&x)[NT][KD]) __attribute__((always_inline)) -> bool {
+    // Step t: x_{t+1} is in LDS, the wave holds its chunks of x_{t+2}.  False
+    // where the loop ends.
+    auto step = [&]() __attribute__((always_inline)) -> bool {
         const SH* hcur = hs[t & 1];
         SH* hnext = hs[(t + 1) & 1];
         if (p.stop_v) {
             // Halting scores of h_t (the operand in LDS, k in order): a row
-            // that ran step t-1 and scores > 0 has ended.  Every lane of a row
-            // computes the same score; lane (row, unit 0) records it.
+            // that ran step t-1 and scores > 0 has ended.  Wave nt forms those
+            // of row tile nt; only its lanes read ended[] of these rows before
+            // lane (row, unit 0) changes it.
             if (t > 0) {
                 if (ran[(t - 1) & 1] == 0) return false;  // no row ran at step t-1: none runs again
                 iters = t;
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    const int n = nt * 16 + (l & 15);
+                if (w < NT) {
+                    const int n = w * 16 + (l & 15);
                     float sc = 0.f;
                     for (int k = 0; k < H; ++k) sc += p.stop_v[k] * EH::to_f32(hcur[n * HS + k]);
                     const bool ends = n < B && t - 1 < len[n] && !ended[n] && sc + p.stop_c > 0.f;
-                    __syncthreads();  // every lane has read ended[] before it changes
-                    if (ends && w == 0 && (l >> 4) == 0) {
+                    if (ends && (l >> 4) == 0) {
                         ended[n] = 1;
                         p.steps[n] = t;
                     }
@@ -236,7 +275,7 @@ small_kernel(SmallParams p) {
                 acc[ks & 1][nt] = EH::mfma(uf[ks], hf, acc[ks & 1][nt]);
             }
         __builtin_amdgcn_sched_barrier(0);
-        project(x);
+        project(t + 1);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
@@ -253,18 +292,15 @@ small_kernel(SmallParams p) {
             }
             hnext[n * HS + u] = EH::from_f32(hst[nt]);
         }
-        if (t + 1 + AHEAD < ml) load_x(x, t + 1 + AHEAD);
+        share_x(t + 2);  // over x_t, read in step t - 1
+        if (t + 3 < ml) load_x(t + 3);
         __syncthreads();
         ++t;
         return t < ml;
     };
     if (ml > 0) {
-        if constexpr (AHEAD == 2)
-            while (step(xa) && step(xb)) {
-            }
-        else
-            while (step(xa)) {
-            }
+        while (step()) {
+        }
     }
 
 #pragma unroll
