@@ -12,7 +12,7 @@ import pytest
 import oracle
 import paper_1810_08061_amd as ld
 import workloads
-from tests.gpu_util import say
+from tests.gpu_util import say, to_device
 from tests.test_gpu_bwd import GRAD_TOL, MODES, compare, scaled_err
 from tests.test_gpu_cells import gru_device
 
@@ -167,3 +167,28 @@ def test_cell_backward_one_launch_reverse_loop(cell):
     g, m = run_train(inp, "persistent", dh, ds)
     assert m.query(ld.Q_LAUNCHES_PER_FORWARD) < 30
     compare(g, oracle_grads(inp, dh, ds), GRAD_TOL["bf16"], keys=KEYS)
+
+
+@pytest.mark.parametrize("cell", ["lstm", "gru", "rnn"])
+@pytest.mark.parametrize("dt,B,H", [("bf16", 20, 1100), ("bf16", 272, 1056), ("f32", 20, 600), ("f32", 300, 40)])
+def test_forward_train_equals_forward_device_wide(dt, B, H, cell):
+    """The same at sizes that take the device-wide loop: one and two gate tiles
+    per workgroup, several chunks of rows.  (Left to the compiler, the cell's
+    multiply-adds were fused the other way round in the two-tile loop that keeps
+    the states, and h differed in its last bit from step 1 on.)"""
+    import torch
+    D, T = 24, 12
+    say(f"case forward for training {dt} B={B} H={H} {cell}")
+    if cell == "lstm":
+        inp = workloads.random_case(1610 + H, B, D, H, T, dtype=dt)
+        dev = to_device(inp)
+    else:
+        inp = workloads.random_cell_case(cell, 1610 + H, B, D, H, T, dtype=dt)
+        dev = (*gru_device(inp), None)
+    m = ld.LstmDyn(B, D, H, T, dt, "persistent", cell=cell)
+    h1, c1, s1 = m.forward_seq(*dev)
+    h2, c2, s2 = m.forward_train(*dev, with_seq=True)
+    torch.cuda.synchronize()
+    assert m.query(ld.Q_LAST_STATUS) == ld.OK
+    assert torch.equal(h1, h2) and torch.equal(c1, c2) and torch.equal(s1, s2)
+    m.close()

@@ -41,7 +41,7 @@ def test_edges(dt, B, D, H, T):
 def test_x_is_gathered_once(dt, D):
     """A step of 64 rows waits for the gathers of x: 12 us with four waves that
     each take all of it (fp32; bf16 17), 17 and 29 with eight, 5.2 where the
-    the workgroup takes it once.  Bound: halfway from that to four."""
+    workgroup takes it once; the bound lies between."""
     T = 200
     say(f"case small step time {dt} D={D}")
     inp = workloads.random_case(9300 + D, 64, D, 32, T, dtype=dt, lo=T)
