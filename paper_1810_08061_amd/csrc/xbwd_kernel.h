@@ -422,12 +422,11 @@ xbwd_kernel(XBwdParams p) {
         f32x4_t z;
         float s, ds;  // the saved state the cell needs (c, GRU: h), the sequence's gradient
     };
-    constexpr int NLOAD = CELL == CELL_RNN ? 2 : 3;  // loads per piece
-    In in[2][PAIRS];                                 // by parity of the steps done
+    In in[2][PAIRS];  // by parity of the steps done
 #pragma unroll
     for (int i = 0; i < PAIRS; ++i) in[0][i] = in[1][i] = In{f32x4_t{0.f, 0.f, 0.f, 0.f}, 0.f, 0.f};
     // The inputs of step tt (first compact row off, act rows); lanes without a
-    // row or unit load another's.  Always NLOAD loads per piece.
+    // row or unit load another's.
     auto load_in = [&](In* dst, int tt, int off, int act) __attribute__((always_inline)) {
         const int rows = rows_of(act);
 #pragma unroll
@@ -510,9 +509,9 @@ xbwd_kernel(XBwdParams p) {
                 v = u32x4{hb[0] | (unsigned)hb[1] << 16, hb[2] | (unsigned)hb[3] << 16, 0u, 0u};
             }
             if (!drained) {
-                // the marks of the last step, made before the loads that may
-                // still be in flight, complete before anything is published
-                if constexpr (!BOTH) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NLOAD * PAIRS) : "memory");
+                // the marks of the last step complete before anything is
+                // published (waves that poll have waited for loads issued after them)
+                if constexpr (!BOTH) drain_stores();
                 drained = true;
             }
             stress_delay(t, 300 + i);

@@ -24,10 +24,12 @@
 //     cell, store their elements of h_{t+1}, and mark the buffer that will
 //     take h_{t+3}.
 // With KW = 4 four further waves are the gate waves: the product waves never
-// store, so their polls wait for nothing but h, and the gate waves never poll,
-// so their Gx (loaded two steps ahead) and their stores are never waited for.
-// With KW = 8 (H > 768: the U slice takes 128 registers of every wave) each
-// wave is both.
+// store, so their polls wait for nothing but h, and the gate waves never poll.
+// Those wait for all that they have in flight before the gates (Gx, loaded two
+// steps ahead, in a branch, so that the compiler's wait covers the load of the
+// next step too) and again before the stores of h (the marks of the last step).
+// With KW = 8 (H > 512: the U slice takes 72 registers of every wave up to H = 768
+// and 128 beyond) each wave is both.
 //
 // The exchange is the device-wide loop's: a ring of four buffers, the marker
 // (all ones, never a value) in every element not yet written, loads at device
@@ -298,7 +300,7 @@ xloop_kernel(XLoopParams p) {
         }
 
     // Gx[tt] of this wave's pairs (tt a step this group runs); lanes without a
-    // row or unit load another's, which is not used.  Always PAIRS loads.
+    // row or unit load another's, which is not used.
     auto load_gx = [&](f32x4_t* dst, int off, int act) __attribute__((always_inline)) {
         const int rows = rows_of(act);
 #pragma unroll
@@ -550,9 +552,9 @@ xloop_kernel(XLoopParams p) {
                 hst[i] = h;
             }
             if (!drained) {
-                // the marks of the last step, made before the Gx loads that
-                // may still be in flight, complete before h_{t+1} is stored
-                if constexpr (!BOTH) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PAIRS) : "memory");
+                // the marks of the last step complete before h_{t+1} is stored
+                // (waves that poll have waited for loads issued after them)
+                if constexpr (!BOTH) drain_stores();
                 drained = true;
             }
             stress_delay(t, 64 + i);
