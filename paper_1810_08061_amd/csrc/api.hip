@@ -850,8 +850,9 @@ static int ensure_train(lstm_dyn* h) {
     tw->xus = xb ? reinterpret_cast<float*>(base + oxus) : nullptr;
     tw->pdh = tw->block_groups ? reinterpret_cast<float*>(base + opdh) : nullptr;
     tw->bar = tw->loop_groups || xb ? reinterpret_cast<unsigned*>(base + obar) : nullptr;
+    // (coherent: a kernel writes the sum of lengths while the host waits for an event)
     if (hipHostMalloc(reinterpret_cast<void**>(&tw->host_offsets), (size_t)(T + 3) * sizeof(int32_t),
-                      hipHostMallocDefault) != hipSuccess) {
+                      hipHostMallocCoherent) != hipSuccess) {
         (void)hipFree(tw->block);
         delete tw;
         return LSTM_DYN_ERR_HIP;

@@ -85,7 +85,8 @@ xbwd_pack_kernel(const typename E::src_t* __restrict__ U, void* ux, float* us, i
             bar[64 * tid + 1] = 0u;
         }
         if (tid < 5) amax[tid] = 0u;
-        if (tid == 64) *host_rows = meta->total_rows;
+        if (tid == 64)  // (for the host, which waits for an event and not for the stream)
+            __hip_atomic_store(host_rows, meta->total_rows, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     const int k = blockIdx.x * 4 + (tid >> 6);
     if (k >= urows) return;

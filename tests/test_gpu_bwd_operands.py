@@ -61,3 +61,28 @@ def test_widths(dt, D, H, B, T, cell, shift):
         assert not g[k].any(), k
     assert torch.equal(g["dh0"], t(dh))
     m.close()
+
+
+@pytest.mark.parametrize("dt,H", [("f32", 40), ("bf16", 200)])
+def test_rows_of_this_call(dt, H):
+    """The GEMMs take as many rows as this forward kept, which a kernel hands to the
+    host while the reverse loop runs: batches of very different sums of lengths,
+    one after another on one handle, give what a fresh handle gives, bit for bit."""
+    import torch
+    B, D, T = 24, 12, 60
+    say(f"case rows of this call {dt} H={H}")
+    dh, dc, _ = upstream(7300 + H, B, H, T)
+    t = lambda a: torch.from_numpy(a).cuda()
+    m = ld.LstmDyn(B, D, H, T, dt, "persistent")
+    for k, hi in enumerate((T, 1, 30, 0, T, 2)):
+        dev = to_device(workloads.random_case(7310 + k, B, D, H, T, dtype=dt, lo=hi // 2, hi=hi))
+        m.forward_train(*dev)
+        g = m.backward(*dev, t(dh), t(dc))
+        f = ld.LstmDyn(B, D, H, T, dt, "persistent")
+        f.forward_train(*dev)
+        g2 = f.backward(*dev, t(dh), t(dc))
+        torch.cuda.synchronize()
+        for n in g:
+            assert torch.equal(g[n], g2[n]), (k, n)
+        f.close()
+    m.close()
