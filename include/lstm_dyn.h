@@ -100,15 +100,34 @@ enum {
     LSTM_DYN_Q_LAST_STATUS = 0,        /* status of the last forward (synchronises its stream) */
     LSTM_DYN_Q_STEPS_EXECUTED = 1,     /* loop iterations of the last forward = max_b L[b] (synchronises) */
     LSTM_DYN_Q_LAUNCHES_PER_FORWARD = 2, /* kernel launches issued by the last forward */
-    LSTM_DYN_Q_GROUPS = 3,             /* workgroups of the persistent kernel */
+    LSTM_DYN_Q_GROUPS = 3,             /* workgroups of the forward's loop launch (per-step handles:
+                                          what the plan below gives) */
     LSTM_DYN_Q_WORKSPACE_BYTES = 4,    /* device workspace owned by the handle */
     LSTM_DYN_Q_TOTAL_ROWS = 5,         /* sum of the (clamped) lengths of the last forward (synchronises) */
     LSTM_DYN_Q_TIME_PREP_NS = 6,       /* with LSTM_DYN_OPT_TIMING: device time of the length
                                           preparation kernel (and, for a GRU or RNN handle, the weight
                                           repacking) in the last forward (synchronises) */
     LSTM_DYN_Q_TIME_INPROJ_NS = 7,     /* ... of the input projection GEMM */
-    LSTM_DYN_Q_TIME_LOOP_NS = 8        /* ... of the time loop (the persistent kernel, or the
+    LSTM_DYN_Q_TIME_LOOP_NS = 8,       /* ... of the time loop (the persistent kernel, or the
                                           per-step path's host loop of launches) */
+    LSTM_DYN_Q_LAST_LOOP = 9           /* which loop the last forward or backward ran (below) */
+};
+
+/* LSTM_DYN_Q_LAST_LOOP: 0 before the first call, then for a forward
+ *   SINGLE   the whole forward in one workgroup,
+ *   GROUPED  one group of workgroups per XCD,
+ *   DEVICE   one loop over all CUs,
+ *   STEPS    launches per step;
+ * for a backward
+ *   REVERSE_GROUPED  one group of workgroups per XCD,
+ *   REVERSE_BLOCKS   one launch over all CUs, column blocks of U,
+ *   REVERSE_FEW      one launch for the last steps, those of at most 16 rows;
+ *                    two launches for each step before them, if any,
+ *   REVERSE_STEPS    two launches per step. */
+enum {
+    LSTM_DYN_LOOP_SINGLE = 1, LSTM_DYN_LOOP_GROUPED = 2, LSTM_DYN_LOOP_DEVICE = 3,
+    LSTM_DYN_LOOP_STEPS = 4, LSTM_DYN_LOOP_REVERSE_GROUPED = 5, LSTM_DYN_LOOP_REVERSE_BLOCKS = 6,
+    LSTM_DYN_LOOP_REVERSE_FEW = 7, LSTM_DYN_LOOP_REVERSE_STEPS = 8
 };
 
 /* lstm_dyn_set_option selectors. */
@@ -124,7 +143,10 @@ enum {
                                     exits normally */
 };
 
-/* Launch plan of a handle: pure host arithmetic, no device access. */
+/* Launch plan: pure host arithmetic, no device access.  mt to nstate describe
+ * the loop over all CUs (or the single workgroup); where a handle's loop runs in
+ * one group of workgroups per XCD instead (LSTM_DYN_Q_LAST_LOOP), its launch has
+ * a shape of its own (LSTM_DYN_Q_GROUPS), and workspace_bytes covers it. */
 typedef struct {
     int mt;             /* 16-column gate tiles per workgroup (4 hidden units each) */
     int groups;         /* workgroups of the persistent kernel (at most one per CU) */

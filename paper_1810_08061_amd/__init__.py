@@ -37,7 +37,9 @@ OK, ERR_INVALID, ERR_HIP, ERR_NOMEM, ERR_UNSUPPORTED, ERR_BAD_LENGTHS, ERR_TIMEO
     ERR_TOO_LARGE = range(8)
 NOALLOC_SCRATCH_BYTES = 128 << 20   # LSTM_DYN_NOALLOC_SCRATCH_BYTES
 Q_LAST_STATUS, Q_STEPS_EXECUTED, Q_LAUNCHES_PER_FORWARD, Q_GROUPS, Q_WORKSPACE_BYTES, \
-    Q_TOTAL_ROWS, Q_TIME_PREP_NS, Q_TIME_INPROJ_NS, Q_TIME_LOOP_NS = range(9)
+    Q_TOTAL_ROWS, Q_TIME_PREP_NS, Q_TIME_INPROJ_NS, Q_TIME_LOOP_NS, Q_LAST_LOOP = range(10)
+LOOP_SINGLE, LOOP_GROUPED, LOOP_DEVICE, LOOP_STEPS, LOOP_REVERSE_GROUPED, LOOP_REVERSE_BLOCKS, \
+    LOOP_REVERSE_FEW, LOOP_REVERSE_STEPS = range(1, 9)
 OPT_TIMING, OPT_STEP_TRACE, OPT_TIMEOUT_US = 0, 1, 2
 
 _DTYPES = {"f32": F32, "fp32": F32, "float32": F32, "bf16": BF16, "bfloat16": BF16}

@@ -117,6 +117,7 @@ struct lstm_dyn {
     unsigned long long timeout_ticks;
     int inproj_grid;           // bf16 data
     long long launches_last;
+    int last_loop;             // LSTM_DYN_LOOP_* of the last forward or backward, or 0
     hipStream_t last_stream;   // the stream of the last forward or backward
     int has_work;              // 1 once work has been enqueued on last_stream
     int timing;                // record phase events on the forward's stream
@@ -616,6 +617,7 @@ static int forward_impl(lstm_dyn_t* h, const void* x, const int32_t* lengths, co
         LD_CHECK(launch_small(d, h->plan.single_kd, h->plan.single_nt, x, lengths, W, U, b, h0, c0,
                               out_h, out_c, out_seq, stop, h->ws, s));
         h->launches_last = 1 + pack_launches;
+        h->last_loop = LSTM_DYN_LOOP_SINGLE;
         LD_CHECK(mark(3));
         if (out_seq) {
             LD_CHECK(launch_seq_finish(d, out_seq, seq_ends, h->num_cus, s));
@@ -634,6 +636,7 @@ static int forward_impl(lstm_dyn_t* h, const void* x, const int32_t* lengths, co
                             out_seq,        stop};
         LD_CHECK(launch_loop(d, h->xl[stop ? 1 : 0], pc, U, h0, c0, out_h, out_c, h->ws, s));
         h->launches_last++;
+        h->last_loop = h->xl[stop ? 1 : 0].variant ? LSTM_DYN_LOOP_GROUPED : LSTM_DYN_LOOP_DEVICE;
         LD_CHECK(mark(3));
         if (out_seq) {  // the loop wrote the valid steps; zeros past each row's last
             LD_CHECK(launch_seq_finish(d, out_seq, seq_ends, h->num_cus, s));
@@ -642,6 +645,7 @@ static int forward_impl(lstm_dyn_t* h, const void* x, const int32_t* lengths, co
         return LSTM_DYN_OK;
     }
     // Per-step comparison path.
+    h->last_loop = LSTM_DYN_LOOP_STEPS;
     LD_CHECK(launch_step_init(d, h0, c0, out_h, out_c, h->ws, s));
     h->launches_last++;
     if (stop) {
@@ -927,8 +931,10 @@ extern "C" int lstm_dyn_forward_train(lstm_dyn_t* h, const void* x, const int32_
                             nullptr,        nullptr,           tw->save_h,  tw->save_c};
         LD_CHECK(launch_loop(d, h->xl[2], pc, U, h0, c0, out_h, out_c, h->ws, s));
         h->launches_last++;
+        h->last_loop = h->xl[2].variant ? LSTM_DYN_LOOP_GROUPED : LSTM_DYN_LOOP_DEVICE;
     } else {
         // the per-step kernels (single-workgroup sizes, per-step handles)
+        h->last_loop = LSTM_DYN_LOOP_STEPS;
         Workspace ws = h->ws;
         if (!ws.z) ws.z = tw->z;
         LD_CHECK(launch_step_init(d, h0, c0, out_h, out_c, ws, s));
@@ -1086,8 +1092,10 @@ extern "C" int lstm_dyn_backward(lstm_dyn_t* h, const void* x, const int32_t* le
                              d_out_h, d_out_c, dh0, dc0, tw->dzx, tw->dzs, tw->amax + 0, tw->bar,
                              h->timeout_ticks, h->trace, h->ws, s));
         h->launches_last++;
+        h->last_loop = LSTM_DYN_LOOP_REVERSE_GROUPED;
         LD_CHECK(hipEventSynchronize(tw->copied));
     } else {
+        h->last_loop = LSTM_DYN_LOOP_REVERSE_STEPS;
         LD_CHECK(hipStreamSynchronize(s));
     }
     const int32_t* off = tw->host_offsets;
@@ -1133,6 +1141,7 @@ extern "C" int lstm_dyn_backward(lstm_dyn_t* h, const void* x, const int32_t* le
                                       tw->dzx, tw->dzs, tw->pdh, tw->amax + 0, h->timeout_ticks, h->trace,
                                       h->ws, s));
             h->launches_last++;
+            h->last_loop = LSTM_DYN_LOOP_REVERSE_BLOCKS;
             t_end = 0;
         } else if (tw->loop_groups) {
             while (t_end > 0 && off[t_end] - off[t_end - 1] <= BWD_LOOP_ROWS) --t_end;
@@ -1145,6 +1154,7 @@ extern "C" int lstm_dyn_backward(lstm_dyn_t* h, const void* x, const int32_t* le
                                      tw->dC, tw->dzx, tw->dzs, tw->bar, h->timeout_ticks, t_end,
                                      h->ws, s));
             h->launches_last++;
+            h->last_loop = LSTM_DYN_LOOP_REVERSE_FEW;
         }
         LD_CHECK(launch_bwd_ones(tw->srow, d.B, s));
         h->launches_last++;
@@ -1207,7 +1217,10 @@ extern "C" int lstm_dyn_query(lstm_dyn_t* h, int what, long long* value) {
     if (!h || !value) return LSTM_DYN_ERR_INVALID;
     switch (what) {
         case LSTM_DYN_Q_LAUNCHES_PER_FORWARD: *value = h->launches_last; return LSTM_DYN_OK;
-        case LSTM_DYN_Q_GROUPS: *value = h->plan.groups; return LSTM_DYN_OK;
+        case LSTM_DYN_Q_GROUPS:
+            *value = h->xl[0].variant ? h->xl[0].gsize << h->xl[0].ng_shift : h->plan.groups;
+            return LSTM_DYN_OK;
+        case LSTM_DYN_Q_LAST_LOOP: *value = h->last_loop; return LSTM_DYN_OK;
         case LSTM_DYN_Q_WORKSPACE_BYTES: *value = h->workspace; return LSTM_DYN_OK;
         case LSTM_DYN_Q_LAST_STATUS:
         case LSTM_DYN_Q_STEPS_EXECUTED:

@@ -1,0 +1,50 @@
+"""Which loop a size takes (LSTM_DYN_Q_LAST_LOOP), forward and back, on both sides
+of each line of the dispatch, and the number of workgroups that its launch has
+(LSTM_DYN_Q_GROUPS)."""
+import numpy as np
+import pytest
+
+import paper_1810_08061_amd as ld
+import workloads
+from tests.gpu_util import say, to_device
+
+pytestmark = pytest.mark.gpu
+
+G, D_, S, SG, RG, RB, RF, RS = (ld.LOOP_GROUPED, ld.LOOP_DEVICE, ld.LOOP_STEPS, ld.LOOP_SINGLE, ld.LOOP_REVERSE_GROUPED,
+                                ld.LOOP_REVERSE_BLOCKS, ld.LOOP_REVERSE_FEW, ld.LOOP_REVERSE_STEPS)
+
+CASES = [  # dt, B, H, mode: forward, workgroups, forward for training, backward
+    ("f32", 64, 32, "persistent", SG, 1, S, RG), ("f32", 65, 32, "persistent", G, 8 * 8, G, RG),
+    ("f32", 8, 256, "persistent", G, 32 * 8, G, RG), ("f32", 256, 512, "persistent", G, 32 * 8, G, RG),
+    ("f32", 257, 512, "persistent", D_, 128, D_, RS), ("f32", 17, 513, "persistent", D_, 129, D_, RS),
+    ("f32", 5, 64, "per_step", S, 16, S, RS),
+    ("bf16", 37, 100, "persistent", G, 25 * 8, G, RG), ("bf16", 257, 512, "persistent", D_, 128, D_, RB),
+    ("bf16", 257, 300, "persistent", D_, 75, D_, RF), ("bf16", 20, 768, "persistent", G, 32 * 8, G, RG),
+    ("bf16", 257, 768, "persistent", D_, 192, D_, RF), ("bf16", 20, 1023, "persistent", G, 32 * 8, G, RG),
+    ("bf16", 20, 1024, "persistent", G, 32 * 8, G, RB), ("bf16", 20, 1026, "persistent", D_, 129, D_, RF),
+    ("bf16", 20, 1025, "persistent", D_, 129, D_, RS), ("bf16", 20, 1280, "persistent", D_, 160, D_, RF),
+    ("bf16", 20, 2048, "persistent", D_, 256, D_, RB), ("bf16", 9, 200, "per_step", S, 50, S, RS),
+]
+
+
+@pytest.mark.parametrize("dt,B,H,mode,fwd,groups,train,bwd", CASES)
+def test_loop_of_size(dt, B, H, mode, fwd, groups, train, bwd):
+    import torch
+    say(f"case loop {dt} B={B} H={H} {mode}")
+    inp = workloads.random_case(9500 + B + H, B, 8, H, 3, dtype=dt)
+    inp.lengths[:] = np.where(np.arange(B) < 16, 3, 2)  # the last step has at most 16 rows
+    dev = to_device(inp)
+    m = ld.LstmDyn(B, 8, H, 3, dt, mode)
+    assert m.query(ld.Q_LAST_LOOP) == 0
+    m.forward(*dev)
+    assert (m.query(ld.Q_LAST_LOOP), m.query(ld.Q_GROUPS)) == (fwd, groups)
+    m.forward_stop(*dev, torch.zeros(H, device="cuda"), -1.0)
+    assert m.query(ld.Q_LAST_LOOP) == fwd
+    m.forward_train(*dev)
+    assert m.query(ld.Q_LAST_LOOP) == train
+    d = torch.ones(B, H, device="cuda")
+    m.backward(*dev, d, d)
+    torch.cuda.synchronize()
+    assert m.query(ld.Q_LAST_STATUS) == ld.OK
+    assert m.query(ld.Q_LAST_LOOP) == bwd
+    m.close()
