@@ -27,16 +27,18 @@ static xloop_fn xloop_of(const XLoopConfig& xc, int cell, int mode) {
 
 // The grouped loop serves whatever a variant covers: bf16 data up to H = 1024
 // and fp32 data up to H = 512 (the U of 32 workgroups is 128 registers of each
-// product wave there), 32 rows per group (two row tiles; more would have the
-// gate waves' state spill, and beyond 256 rows the device-wide loop's chunks
-// are full).  It was faster at every size measured within these but one: fp32
-// beyond H = 384 with a single row tile in all, where its MFMAs (1.7 us a step
-// and tile, U over 32 CUs) cost more than the exchange through memory saves
-// (whole forwards of 100 full steps at H = 512: 8 rows 336 against 302 us, 64
-// rows 374 against 527; H = 384, 3 rows: 242 against 312).
+// product wave there), 32 rows per group (beyond, the device-wide loop's chunks
+// are full; with two row tiles the widest variants already spill: 8 to 20
+// registers at fp32 H = 512 and 2 to 25 at bf16 H = 1024, with termination or for
+// training).  Against the device-wide loop, whole forwards of 100 full steps:
+// fp32 H 512, 1 row 314 and 248 us, 8 rows 315 and 269, 16 rows 321 and 268, 64
+// rows 527 and 374; H 385, 8 rows 304 and 259; bf16 H 513, 8 rows 259 and 225,
+// 24 rows 320 and 231.  The one place where it is not faster is bf16 beyond H =
+// 768 with up to 16 rows, where the two are within 3% of each other (H 1024, 8
+// rows: 260 and 269; with termination 303 and 297, GRU 258 and 247, a training
+// step 979 and 882).
 bool xloop_pick(const Dims& d, int num_cus, XLoopConfig* xc) {
     *xc = XLoopConfig{};
-    if (!d.bf16 && d.H > 384 && d.B <= 16) return false;
     int shift = 3;
     while (shift >= 0 && (X_GROUP << shift) > num_cus) --shift;
     if (shift < 0) return false;

@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("H,B", [(33, 1), (64, 5), (65, 31), (128, 32), (129, 33), (256, 32), (255, 4), (257, 8),
-                                 (384, 30), (385, 32), (512, 25)])
+                                 (384, 30), (385, 32), (512, 25), (385, 16), (400, 3), (512, 1), (511, 9), (512, 16)])
 def test_edges(H, B):
     import torch
     D, T = 12, 10

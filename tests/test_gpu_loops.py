@@ -16,6 +16,7 @@ G, D_, S, SG, RG, RB, RF, RS = (ld.LOOP_GROUPED, ld.LOOP_DEVICE, ld.LOOP_STEPS, 
 CASES = [  # dt, B, H, mode: forward, workgroups, forward for training, backward
     ("f32", 64, 32, "persistent", SG, 1, S, RG), ("f32", 65, 32, "persistent", G, 8 * 8, G, RG),
     ("f32", 8, 256, "persistent", G, 32 * 8, G, RG), ("f32", 256, 512, "persistent", G, 32 * 8, G, RG),
+    ("f32", 1, 512, "persistent", G, 32 * 8, G, RG), ("f32", 16, 385, "persistent", G, 25 * 8, G, RG),
     ("f32", 257, 512, "persistent", D_, 128, D_, RS), ("f32", 17, 513, "persistent", D_, 129, D_, RS),
     ("f32", 5, 64, "per_step", S, 16, S, RS),
     ("bf16", 37, 100, "persistent", G, 25 * 8, G, RG), ("bf16", 257, 512, "persistent", D_, 128, D_, RB),
