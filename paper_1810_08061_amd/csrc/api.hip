@@ -62,17 +62,17 @@ struct TrainWs {
     float* xh;      // fp32: [B*T][D + H] x and h_prev side by side, over save_c
                     // and xc (after the loop, before the rows of dx)
     float* w_il;    // fp32: [D][4H] W, gate-interleaved columns
-    float* u_il;    // [H][4H] U, likewise
+    float* u_il;    // [H][4H] U, likewise (this and dH, dC: not with the grouped reverse loop)
     float* dwu_il;  // [D + H][4H] weight gradients, gate-interleaved columns
     float* cs_part; // [BWD_CS_CHUNKS][4H] partial column sums of dz
     float* dH;      // [B][H] gradient of h in slot order
     float* dC;      // [B][H]
-    float* z;       // [bpad][4H] per-step pre-activations (handles not in per-step mode)
+    float* z;       // [bpad][4H] per-step pre-activations (persistent handles that train per step)
     // bf16 data: fp16 operands of the weight-gradient GEMMs (scaled by powers of two)
     _Float16* dz16; // [B*T][4H]
     _Float16* xh16; // [B*T][D + H] x and h_prev
     _Float16* w16;  // [D][4H]
-    _Float16* u16;  // [H][4H] U (gate-interleaved), scaled
+    _Float16* u16;  // [H][4H] U (gate-interleaved), scaled (this, dzs16, srow: not with the grouped loop)
     _Float16* dzs16;// [B][4H] one step's dz, each row scaled by srow
     float* srow;    // [B] scale of each row's dH
     unsigned* amax; // [BWD_MAX_WORDS] [0..4]: largest magnitudes (float bits) of dz, x, h_prev, W, U
@@ -796,17 +796,22 @@ static int ensure_train(lstm_dyn* h) {
         o = align_up(o + bytes, 256);
         return at;
     };
-    const long long oh = take(4 * B * T * H), oc = take(4 * B * T * H), ox = take(4 * B * T * D),
-                    ow = take(4 * D * 4 * H), ou = take(4 * H * 4 * H), odwu = take(4 * (D + H) * 4 * H),
-                    odh = take(4 * B * H), odc = take(4 * B * H), oz = take(16 * H * bpad);
     const bool h16 = h->dtype == LSTM_DYN_BF16;
-    const long long odz16 = take(h16 ? 2 * B * T * 4 * H : 0), oxh16 = take(h16 ? 2 * B * T * (D + H) : 0),
-                    ow16 = take(h16 ? 2 * D * 4 * H : 0),
-                    ou16 = take(h16 ? 2 * H * 4 * H : 0), odzs = take(h16 ? 2 * B * 4 * H : 0),
-                    osr = take(4 * B), osm = take(4 * BWD_MAX_WORDS), ocs = take(4LL * BWD_CS_CHUNKS * 4 * H);
     const bool pers16 = h16 && h->mode == LSTM_DYN_PERSISTENT;
     if (h->mode == LSTM_DYN_PERSISTENT) (void)xbwd_pick(h->dims, h->num_cus, &tw->xb);
     const bool xb = tw->xb.variant != nullptr;
+    // what the grouped reverse loop does without: U and dz as GEMM operands of
+    // each step, the gradients in slot order
+    const bool steps = !xb, steps16 = steps && h16;
+    const bool own_z = h->mode == LSTM_DYN_PERSISTENT && (h->plan.single || !h->save_ok);
+    const long long oh = take(4 * B * T * H), oc = take(4 * B * T * H), ox = take(4 * B * T * D),
+                    ow = take(h16 ? 0 : 4 * D * 4 * H), ou = take(steps ? 4 * H * 4 * H : 0),
+                    odwu = take(4 * (D + H) * 4 * H), odh = take(steps ? 4 * B * H : 0),
+                    odc = take(steps ? 4 * B * H : 0), oz = take(own_z ? 16 * H * bpad : 0);
+    const long long odz16 = take(h16 ? 2 * B * T * 4 * H : 0), oxh16 = take(h16 ? 2 * B * T * (D + H) : 0),
+                    ow16 = take(h16 ? 2 * D * 4 * H : 0), ou16 = take(steps16 ? 2 * H * 4 * H : 0),
+                    odzs = take(steps16 ? 2 * B * 4 * H : 0), osr = take(steps16 ? 4 * B : 0),
+                    osm = take(4 * BWD_MAX_WORDS), ocs = take(4LL * BWD_CS_CHUNKS * 4 * H);
     tw->block_groups = pers16 && !xb ? bwd_block_fits(h->dims, h->num_cus) : 0;
     tw->loop_groups = pers16 && !xb && !tw->block_groups ? bwd_loop_fits(h->dims, h->num_cus) : 0;
     int kp = 0, nblk = 0;
@@ -833,20 +838,20 @@ static int ensure_train(lstm_dyn* h) {
     tw->save_h = reinterpret_cast<float*>(base + oh);
     tw->save_c = reinterpret_cast<float*>(base + oc);
     tw->xc = reinterpret_cast<float*>(base + ox);
-    tw->w_il = reinterpret_cast<float*>(base + ow);
-    tw->u_il = reinterpret_cast<float*>(base + ou);
+    tw->w_il = h16 ? nullptr : reinterpret_cast<float*>(base + ow);
+    tw->u_il = steps ? reinterpret_cast<float*>(base + ou) : nullptr;
     tw->xh = tw->save_c;
     tw->dwu_il = reinterpret_cast<float*>(base + odwu);
     tw->cs_part = reinterpret_cast<float*>(base + ocs);
-    tw->dH = reinterpret_cast<float*>(base + odh);
-    tw->dC = reinterpret_cast<float*>(base + odc);
-    tw->z = reinterpret_cast<float*>(base + oz);
+    tw->dH = steps ? reinterpret_cast<float*>(base + odh) : nullptr;
+    tw->dC = steps ? reinterpret_cast<float*>(base + odc) : nullptr;
+    tw->z = own_z ? reinterpret_cast<float*>(base + oz) : nullptr;
     tw->dz16 = h16 ? reinterpret_cast<_Float16*>(base + odz16) : nullptr;
     tw->xh16 = h16 ? reinterpret_cast<_Float16*>(base + oxh16) : nullptr;
     tw->w16 = h16 ? reinterpret_cast<_Float16*>(base + ow16) : nullptr;
-    tw->u16 = h16 ? reinterpret_cast<_Float16*>(base + ou16) : nullptr;
-    tw->dzs16 = h16 ? reinterpret_cast<_Float16*>(base + odzs) : nullptr;
-    tw->srow = reinterpret_cast<float*>(base + osr);
+    tw->u16 = steps16 ? reinterpret_cast<_Float16*>(base + ou16) : nullptr;
+    tw->dzs16 = steps16 ? reinterpret_cast<_Float16*>(base + odzs) : nullptr;
+    tw->srow = steps16 ? reinterpret_cast<float*>(base + osr) : nullptr;
     tw->amax = reinterpret_cast<unsigned*>(base + osm);
     tw->dzx = one_launch || xb ? reinterpret_cast<_Float16*>(base + odzx) : nullptr;
     tw->dzs = one_launch || xb ? reinterpret_cast<float*>(base + odzsc) : nullptr;

@@ -49,3 +49,32 @@ def test_loop_of_size(dt, B, H, mode, fwd, groups, train, bwd):
     assert m.query(ld.Q_LAST_STATUS) == ld.OK
     assert m.query(ld.Q_LAST_LOOP) == bwd
     m.close()
+
+
+@pytest.mark.parametrize("dt,B,D,H,T", [("bf16", 20, 24, 1000, 3), ("bf16", 64, 40, 512, 5), ("f32", 9, 30, 500, 3),
+                                        ("f32", 64, 16, 32, 4)])
+def test_training_workspace(dt, B, D, H, T):
+    """A handle with the grouped reverse loop reserves for training what it uses:
+    the kept states and rows, the GEMMs' operands and results, the column sums,
+    U packed, the exchange of dz; no operands of a product per step."""
+    say(f"case training workspace {dt} B={B} D={D} H={H} T={T}")
+    dev = to_device(workloads.random_case(9700 + H, B, D, H, T, dtype=dt))
+    m = ld.LstmDyn(B, D, H, T, dt, "persistent")
+    before = m.query(ld.Q_WORKSPACE_BYTES)
+    m.forward_train(*dev)
+    got = m.query(ld.Q_WORKSPACE_BYTES) - before
+    e = 2 if dt == "bf16" else 4
+    rows, slots = B * T, -(-B // 8) * 8
+    need = 8 * rows * H + 4 * rows * D + 16 * (D + H) * H + 16 * D * H * e // 4 + 64 * 16 * H   # states, dx, dW dU, W, sums
+    if dt == "bf16":
+        need += 2 * rows * (D + 5 * H)                                    # dz, x and h in fp16
+    pad = next(w for w in (512, 1024, 2048, 4096) if w >= 4 * H)          # 4H as the compiled variants pad it
+    need += e * (H + 32) * pad + 4 * e * slots * pad + 4 * H              # U packed, dz exchanged, U's scales
+    if dt == "bf16":
+        need += 8 * slots * (pad // 32)
+    if H <= 32:
+        need += 16 * H * (-(-B // 16) * 16)                               # pre-activations of a step
+    need += 24 * 256                                                      # each array starts at a multiple of 256 bytes
+    say(f"  {got} bytes, at most {need} used")
+    assert got <= need
+    m.close()
