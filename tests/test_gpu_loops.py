@@ -78,3 +78,37 @@ def test_training_workspace(dt, B, D, H, T):
     say(f"  {got} bytes, at most {need} used")
     assert got <= need
     m.close()
+
+
+@pytest.mark.parametrize("dt,H", [("bf16", 512), ("f32", 256)])
+def test_two_handles_on_two_streams(dt, H):
+    """Two handles whose launches each take every CU, forward and back on streams of
+    their own without a wait between them: each gives what it gives alone."""
+    import torch
+    B, D, T = 40, 32, 50
+    say(f"case two streams {dt} H={H}")
+    d = torch.ones(B, H, device="cuda")
+    dev = [to_device(workloads.random_case(9800 + k, B, D, H, T, dtype=dt)) for k in range(2)]
+    ms = [ld.LstmDyn(B, D, H, T, dt, "persistent") for _ in range(2)]
+    alone = []
+    for m, a in zip(ms, dev):
+        m.set_option(ld.OPT_TIMEOUT_US, 500000)
+        h, c = m.forward(*a)
+        m.forward_train(*a)
+        alone.append({"h": h, "c": c, **m.backward(*a, d, d)})
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    got = [None, None]
+    for rep in range(5):
+        for k in (0, 1):
+            with torch.cuda.stream(streams[k]):
+                h, c = ms[k].forward(*dev[k])
+                ms[k].forward_train(*dev[k])
+                got[k] = {"h": h, "c": c, **ms[k].backward(*dev[k], d, d)}
+        torch.cuda.synchronize()
+        for k in (0, 1):
+            assert ms[k].query(ld.Q_LAST_STATUS) == ld.OK
+            for n in alone[k]:
+                assert torch.equal(got[k][n], alone[k][n]), (rep, k, n)
+    for m in ms:
+        m.close()
