@@ -218,17 +218,20 @@ def test_backward_exact_facts(mode):
         m.backward(*dev, zt, zt)
 
 
+@pytest.mark.parametrize("H,loop", [(96, ld.LOOP_REVERSE_GROUPED), (1100, ld.LOOP_REVERSE_FEW)],
+                         ids=["grouped", "few-row"])
 @pytest.mark.parametrize("seq", [True, False], ids=["dseq", "final-state"])
-def test_backward_one_launch_reverse_loop(seq):
-    """bf16 data, at most 16 rows in every step, H even and above 64 but not
-    a multiple of 256: the whole reverse loop is the launch for the steps
-    with few rows (dh0 from the launch itself); against the oracle, and
-    against the per-step path's launch count."""
-    B, D, H, T = 9, 20, 96, 40
+def test_backward_one_launch_reverse_loop(seq, H, loop):
+    """bf16 data, at most 16 rows in every step: the whole reverse loop is one
+    launch (dh0 from the launch itself), in one group per XCD at H = 96, the one
+    for the steps with few rows at H = 1100; against the oracle, and against the
+    per-step path's launch count."""
+    B, D, T = 9, 20, 40
     inp = workloads.random_case(1201, B, D, H, T, dtype="bf16", lo=20)
     dh, dc, ds = upstream(2201, B, H, T, seq)
     say(f"case bwd one-launch loop seq={seq} lengths={inp.lengths.tolist()}")
     g, _, m = run_train(inp, "persistent", dh, dc, ds)
+    assert m.query(ld.Q_LAST_LOOP) == loop
     launches = m.query(ld.Q_LAUNCHES_PER_FORWARD)
     go = oracle_grads(inp, dh.astype(np.float64), dc.astype(np.float64),
                       ds.astype(np.float64) if ds is not None else None)
@@ -239,21 +242,41 @@ def test_backward_one_launch_reverse_loop(seq):
     assert launches < 30 <= 2 * int(inp.lengths.max()) <= per_step
 
 
+@pytest.mark.parametrize("H", [16, 66, 96, 300, 700])
+def test_backward_few_row_launch_after_many_rows(H):
+    """More rows than the grouped loop holds, few of them long: the last steps are
+    the launch for few rows, the ones before them two launches each, which take
+    over its dh and dc.  Each compiled width of that launch below 1024."""
+    B, D, T = 257 + H % 5, 12, 30
+    inp = workloads.random_case(1221 + H, B, D, H, T, dtype="bf16", hi=5)
+    inp.lengths[3:15] = np.arange(19, 31)
+    dh, dc, ds = upstream(2221 + H, B, H, T)
+    say(f"case bwd few-row launch behind {B} rows H={H}")
+    g, _, m = run_train(inp, "persistent", dh, dc, ds)
+    assert m.query(ld.Q_LAST_LOOP) == ld.LOOP_REVERSE_FEW
+    assert 2 * 5 <= m.query(ld.Q_LAUNCHES_PER_FORWARD) < 2 * 5 + 20
+    compare(g, oracle_grads(inp, dh.astype(np.float64), dc.astype(np.float64), ds.astype(np.float64)), GRAD_TOL["bf16"])
+    m.close()
+
+
+@pytest.mark.parametrize("B,H,loop", [(96, 256, ld.LOOP_REVERSE_GROUPED), (300, 256, ld.LOOP_REVERSE_BLOCKS),
+                                      (260, 512, ld.LOOP_REVERSE_BLOCKS), (40, 1024, ld.LOOP_REVERSE_BLOCKS)])
 @pytest.mark.parametrize("seq", [True, False], ids=["dseq", "final-state"])
-def test_backward_whole_loop_launch(seq):
-    """bf16 data, H a multiple of 256: the whole reverse loop is one
-    cooperative launch with column blocks of U, whatever the rows per step
-    (up to 96 here); every gradient against the oracle, the launch count
-    against the per-step path's, and a second run bit for bit equal to the
-    first (the shares of dh and the waves' partial sums are added in a fixed
-    order, whatever the order in which the data arrive)."""
-    B, D, H, T = 96, 40, 256, 30
+def test_backward_whole_loop_launch(seq, B, H, loop):
+    """bf16 data: the whole reverse loop is one cooperative launch, in one group per
+    XCD or (256, 512 and 1024 of it with more rows or units than those hold) with
+    column blocks of U, whatever the rows per step; every gradient against the
+    oracle, the launch count against the per-step path's, and a second run bit for
+    bit equal to the first (the shares of dh and the waves' partial sums are added
+    in a fixed order, whatever the order in which the data arrive)."""
+    D, T = 40, 30 if B < 100 else 16
     inp = workloads.random_case(1211, B, D, H, T, dtype="bf16")
     dh, dc, ds = upstream(2211, B, H, T, seq)
     L = inp.lengths
     say(f"case bwd whole-loop launch seq={seq} rows per step "
         f"{[int((L > t).sum()) for t in range(0, T, 5)]}")
     g, _, m = run_train(inp, "persistent", dh, dc, ds)
+    assert m.query(ld.Q_LAST_LOOP) == loop
     launches = m.query(ld.Q_LAUNCHES_PER_FORWARD)
     go = oracle_grads(inp, dh.astype(np.float64), dc.astype(np.float64),
                       ds.astype(np.float64) if ds is not None else None)
@@ -270,19 +293,26 @@ def test_backward_whole_loop_launch(seq):
 
 
 @pytest.mark.parametrize("scale", [1e-6, 1e6, 1e12])
-@pytest.mark.parametrize("mode", MODES)
-def test_backward_upstream_magnitude(scale, mode):
+@pytest.mark.parametrize("mode,B,H,loop", [("persistent", 33, 100, ld.LOOP_REVERSE_GROUPED),
+                                           ("persistent", 33, 600, ld.LOOP_REVERSE_GROUPED),
+                                           ("persistent", 33, 1100, ld.LOOP_REVERSE_FEW),
+                                           ("persistent", 260, 100, ld.LOOP_REVERSE_FEW),
+                                           ("persistent", 33, 1024, ld.LOOP_REVERSE_BLOCKS),
+                                           ("per_step", 33, 100, ld.LOOP_REVERSE_STEPS)])
+def test_backward_upstream_magnitude(scale, mode, B, H, loop):
     """Gradients are linear in the upstream gradients: scaled by 1e-6 to 1e12
     they are scaled alike, and the fp16 operands of the bf16 path (powers of
     two per operand, per row and per row block) neither overflow nor lose
-    the largest entries.  With H = 100 the persistent handle runs the steps
-    with at most 16 rows in one launch and the others on the per-step path."""
-    B, D, H, T = 33, 40, 100, 14
+    the largest entries, in any of the reverse loops."""
+    D, T = 40, 14
     inp = workloads.random_case(1401, B, D, H, T, dtype="bf16")
+    if B > 256:
+        inp.lengths[10:] = np.minimum(inp.lengths[10:], 9)   # the last steps have few rows
     dh, dc, ds = upstream(2401, B, H, T)
     dh, dc, ds = dh * np.float32(scale), dc * np.float32(scale), ds * np.float32(scale)
-    say(f"case bwd upstream x{scale:g} {mode}")
-    g, _, _ = run_train(inp, mode, dh, dc, ds)
+    say(f"case bwd upstream x{scale:g} {mode} B={B} H={H}")
+    g, _, m = run_train(inp, mode, dh, dc, ds)
+    assert m.query(ld.Q_LAST_LOOP) == loop
     for k in g:
         assert np.all(np.isfinite(g[k])), k
     go = oracle_grads(inp, dh.astype(np.float64), dc.astype(np.float64), ds.astype(np.float64))

@@ -1,7 +1,8 @@
 """Randomised parity sweep where a step spans several chunks of row tiles:
 129 to 512 rows of bf16 LSTM data on persistent handles, hidden widths 256
-and 512 (the whole reverse loop in one launch; above 256 padded rows it keeps
-the carried gradients in memory), ragged lengths, with and without the
+and 512 (up to 256 rows both loops run in one group per XCD with two row tiles,
+above that over all CUs, the reverse loop with column blocks of U and the carried
+gradients in memory), ragged lengths, with and without the
 output sequence's gradient.  The forward for training (final state and
 output sequence) and every gradient against the fp64 oracle; the same for
 the GRU and tanh RNN cells' gradients.  Also the forward at the widest
@@ -12,6 +13,7 @@ import numpy as np
 import pytest
 
 import oracle
+import paper_1810_08061_amd as ld
 import workloads
 from tests.gpu_util import max_err, say
 from tests.test_gpu_bwd import GRAD_TOL, compare, oracle_grads, run_train
@@ -51,6 +53,7 @@ def test_random_large_batch(k):
     go = oracle_grads(inp, dh.astype(np.float64), dc.astype(np.float64),
                       ds.astype(np.float64) if ds is not None else None)
     compare(g, go, GRAD_TOL[workloads.BF16])
+    assert m.query(ld.Q_LAST_LOOP) == (ld.LOOP_REVERSE_GROUPED if B <= 256 else ld.LOOP_REVERSE_BLOCKS)
     m.close()
 
 
@@ -65,6 +68,7 @@ def test_random_large_batch_cells(k):
     ds = rng.standard_normal((B, T, H)).astype(np.float32) if seq else None
     g, m = cell_run(inp, "persistent", dh, ds)
     compare(g, cell_oracle(inp, dh, ds), GRAD_TOL[workloads.BF16], keys=CELL_KEYS)
+    assert m.query(ld.Q_LAST_LOOP) == (ld.LOOP_REVERSE_GROUPED if B <= 256 else ld.LOOP_REVERSE_BLOCKS)
     m.close()
 
 
@@ -85,7 +89,6 @@ def _draw_wide(k):
 def test_random_wide_forward(k):
     import torch
     from tests.gpu_util import to_device
-    import paper_1810_08061_amd as ld
     B, D, H, T, dt, mode = _draw_wide(k)
     say(f"case random wide {k}: B={B} D={D} H={H} T={T} {dt} {mode}")
     inp = workloads.random_case(9650 + k, B, D, H, T, dtype=dt)

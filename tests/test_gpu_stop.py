@@ -30,15 +30,15 @@ TOL = {workloads.F32: 1e-5, workloads.BF16: 3e-3}
 MODES = ["persistent", "per_step"]
 
 
-def _inputs(cell, inp):
+def _inputs(cell, inp, on_device=True):
     """(device args without c0, oracle args) for a batch of one cell."""
     x, W, U = inp.as_f32()
     if cell == "lstm":
-        dev = to_device(inp)
+        dev = to_device(inp) if on_device else [None] * 7
         return dev[:6], dev[6], dict(x=x, W=W, U=U, b=inp.b, h0=inp.h0, c0=inp.c0, b_hh=None)
     c0 = np.zeros_like(inp.h0)
     b = inp.b_ih if cell == "gru" else inp.b
-    return gru_device(inp), None, dict(x=x, W=W, U=U, b=b, h0=inp.h0, c0=c0,
+    return gru_device(inp) if on_device else None, None, dict(x=x, W=W, U=U, b=b, h0=inp.h0, c0=c0,
                                         b_hh=inp.b_hh if cell == "gru" else None)
 
 
@@ -139,6 +139,34 @@ def test_stop_small_shapes(shape, mode, cell):
 
 
 @pytest.mark.parametrize("cell", ["lstm", "gru", "rnn"])
+@pytest.mark.parametrize("B,H,T,dt,loop", [
+    (140, 300, 12, "f32", ld.LOOP_GROUPED), (256, 64, 20, "f32", ld.LOOP_GROUPED),
+    (200, 512, 10, "f32", ld.LOOP_GROUPED), (32, 256, 15, "f32", ld.LOOP_GROUPED),
+    (129, 130, 16, "bf16", ld.LOOP_GROUPED), (256, 512, 12, "bf16", ld.LOOP_GROUPED),
+    (200, 768, 10, "bf16", ld.LOOP_GROUPED), (256, 1000, 8, "bf16", ld.LOOP_GROUPED),
+    (300, 100, 14, "bf16", ld.LOOP_DEVICE), (272, 512, 9, "bf16", ld.LOOP_DEVICE),
+    (257, 1024, 6, "bf16", ld.LOOP_DEVICE), (300, 200, 9, "f32", ld.LOOP_DEVICE)])
+def test_stop_row_tiles(B, H, T, dt, loop, cell):
+    """Rows that end on their state one after another, in the grouped loop with two
+    row tiles (more than 128 rows) and with products of four rows (fp32, up to 32),
+    and in the device-wide loop behind it with one gate tile per workgroup.  c lets
+    six rows of ten end, by the largest score on their way."""
+    inp = _case(cell, 760 + B + H, B, 16, H, T, dt)
+    v, _ = _readout(860 + H, H, 0.0)
+    score = _plain_trace(cell, _inputs(cell, inp, False)[2], inp.lengths, None) @ v.astype(np.float64)
+    best = np.where(np.arange(T)[None, :] < inp.lengths[:, None], score, -np.inf).max(1)
+    c = float(np.float32(-np.quantile(best[inp.lengths > 0], 0.4)))
+    say(f"case stop row tiles {cell} B={B} H={H} {dt}")
+    h, cs, steps, seq, iters, m = run_stop(inp, cell, "persistent", v, c, seq=True)
+    assert m.query(ld.Q_LAST_LOOP) == loop
+    ties = check_against_oracle(cell, inp, v, c, h, cs, steps, seq, iters, TOL[dt])
+    early = int((steps < np.clip(inp.lengths, 0, T)).sum())
+    say(f"  rows ended early: {early}/{B}, iters={iters}, near-ties={ties}")
+    assert early >= 4 and len(np.unique(steps)) >= 4
+    m.close()
+
+
+@pytest.mark.parametrize("cell", ["lstm", "gru", "rnn"])
 @pytest.mark.parametrize("mode", MODES)
 @pytest.mark.parametrize("name", workloads.ORDER)
 def test_stop_workloads(name, mode, cell):
@@ -207,13 +235,13 @@ def test_all_caps_zero(mode):
     assert np.array_equal(h, inp.h0) and np.array_equal(cs, inp.c0)
 
 
-@pytest.mark.parametrize("mode", MODES)
-def test_early_exit_ends_the_loop(mode):
+@pytest.mark.parametrize("mode,B", [("persistent", 64), ("per_step", 64), ("persistent", 256)])
+def test_early_exit_ends_the_loop(mode, B):
     """Caps of 200 steps but every row ends within a few: the loop stops at
     the last row's end, far below the cap."""
-    inp = workloads.random_case(84, 64, 64, 128, 200, dtype="bf16", lo=200)
+    inp = workloads.random_case(84, B, 64, 128, 200, dtype="bf16", lo=200)
     v, c = _readout(85, 128, -0.2)
-    v = np.abs(v)                                  # the fp64 oracle ends every row by step 55
+    v = np.abs(v)                                  # the fp64 oracle ends every row by step 55 (64 rows)
     h, cs, steps, seq, iters, m = run_stop(inp, "lstm", mode, v, c, seq=True)
     check_against_oracle("lstm", inp, v, c, h, cs, steps, seq, iters, 3e-3)
     say(f"  iters={iters} steps max={int(steps.max())} min={int(steps.min())}")

@@ -14,9 +14,13 @@ from tests.gpu_util import say, to_device
 pytestmark = pytest.mark.gpu
 
 
-def test_forward_wait_bound():
+@pytest.mark.parametrize("B,H,loop", [(64, 512, ld.LOOP_GROUPED), (256, 2048, ld.LOOP_DEVICE)],
+                         ids=["grouped", "device-wide"])
+def test_forward_wait_bound(B, H, loop):
+    """Both loops' polls.  (The device-wide one at 256 rows of H = 2048, where a step
+    takes 13 us of which a workgroup waits several for the slowest.)"""
     import torch
-    inp = workloads.random_case(1301, 64, 32, 512, 120, dtype="bf16", lo=60)
+    inp = workloads.random_case(1301, B, 32, H, 120, dtype="bf16", lo=60)
     dev = to_device(inp)
     m = ld.LstmDyn(inp.B, inp.D, inp.H, inp.T, inp.dtype, "persistent")
     m.set_option(ld.OPT_TIMEOUT_US, 1)
@@ -24,6 +28,7 @@ def test_forward_wait_bound():
     m.forward(*dev)
     torch.cuda.synchronize()
     assert m.query(ld.Q_LAST_STATUS) == ld.ERR_TIMEOUT
+    assert m.query(ld.Q_LAST_LOOP) == loop
     m.set_option(ld.OPT_TIMEOUT_US, 0)
     h, c = m.forward(*dev)
     torch.cuda.synchronize()
@@ -36,11 +41,15 @@ def test_forward_wait_bound():
     f.close()
 
 
-@pytest.mark.parametrize("B,H", [(256, 2048), (16, 96)], ids=["whole-loop-launch", "few-row-launch"])
-def test_backward_wait_bound(B, H):
+@pytest.mark.parametrize("B,H,loop", [(256, 2048, ld.LOOP_REVERSE_BLOCKS), (16, 1100, ld.LOOP_REVERSE_FEW),
+                                      (16, 96, ld.LOOP_REVERSE_GROUPED), (64, 512, ld.LOOP_REVERSE_GROUPED),
+                                      (200, 1000, ld.LOOP_REVERSE_GROUPED)],
+                         ids=["whole-loop-launch", "few-row-launch", "grouped-96", "grouped-512", "grouped-1000"])
+def test_backward_wait_bound(B, H, loop):
     """The reverse loop's cooperative launches (bf16 data): the whole loop
-    with column blocks of U (H a multiple of 256), and the launch for the
-    steps with at most 16 rows (other H).  Past the bound the launch stops
+    with column blocks of U, the launch for the steps with at most 16 rows
+    (16 rows here: all steps), and the loop in one group per XCD, with cell
+    waves of their own and without.  Past the bound the launch stops
     with ERR_TIMEOUT; with the bound restored the gradients equal a fresh
     handle's bit for bit.  The whole-loop launch has no grid barrier: its
     waits are those of one workgroup for another's data, which at a few rows
@@ -67,6 +76,7 @@ def test_backward_wait_bound(B, H):
     m.backward(*dev, dh, dc)
     torch.cuda.synchronize()
     assert m.query(ld.Q_LAST_STATUS) == ld.ERR_TIMEOUT
+    assert m.query(ld.Q_LAST_LOOP) == loop
     m.set_option(ld.OPT_TIMEOUT_US, 0)
     g = grads(m)
     assert m.query(ld.Q_LAST_STATUS) == ld.OK
