@@ -33,8 +33,8 @@ struct GemmParams {
     const int32_t* rowsrc;
     const int32_t* offsets;
     int K, lda, H, t;
-    int a_vec, b_vec;      // 16-byte vector loads allowed for the A rows / B rows
-    int small_below;       // small tiles where there are fewer large ones than this
+    int a_vec, b_vec;      // the A rows / the gates' runs of a B row are whole, aligned 16-byte vectors
+    int small_upto;        // small tiles where there are at most this many large ones
 };
 
 // T: c' and rows per tile, BKB: bytes of K per block.
@@ -111,11 +111,18 @@ __device__ __forceinline__ void gemm_tiles(const GemmParams& p, int nrows, int r
 #pragma unroll
             for (int j = 0; j < AV; ++j) {
                 const int k = k0 + aseg[j] * VE;
-                if (arow_ok[j] && p.a_vec && k + VE <= K) {
-                    const uint4 v = *reinterpret_cast<const uint4*>(arow[j] + k);
+                // Rows of whole 16-byte vectors: past the end another is taken and not
+                // used, so that no load waits behind a branch.  Else the same loads at
+                // the elements' alignment, and one by one at a row's end (one by one
+                // throughout, 2115 tiles at H 257, D 400 took 404 us, and 362 so).
+                if (p.a_vec) {
+                    const bool ok = arow_ok[j] && k < K;
+                    const uint4 v = *reinterpret_cast<const uint4*>(arow[j] + (k < K ? k : 0));
                     const S* vs = reinterpret_cast<const S*>(&v);
 #pragma unroll
-                    for (int e = 0; e < VE; ++e) areg[j][e] = vs[e];
+                    for (int e = 0; e < VE; ++e) areg[j][e] = ok ? vs[e] : E::from_f32(0.0f);
+                } else if (arow_ok[j] && k + VE <= K) {
+                    __builtin_memcpy(areg[j], arow[j] + k, 16);
                 } else {
 #pragma unroll
                     for (int e = 0; e < VE; ++e)
@@ -123,16 +130,18 @@ __device__ __forceinline__ void gemm_tiles(const GemmParams& p, int nrows, int r
                 }
                 const int kb = k0 + bkk[j];
                 const int u = ubase + bseg[j] * VE;
-                const Src* src = Bw + (long)kb * N4 + bg[j] * H + u;
-                if (kb < K && p.b_vec && u + VE <= H) {
-                    const uint4 v = *reinterpret_cast<const uint4*>(src);
+                const Src* src = Bw + (long)min(kb, K - 1) * N4 + bg[j] * H;
+                if (p.b_vec) {
+                    const bool ok = kb < K && u < H;
+                    const uint4 v = *reinterpret_cast<const uint4*>(src + (u < H ? u : 0));
                     const Src* vs = reinterpret_cast<const Src*>(&v);
 #pragma unroll
-                    for (int e = 0; e < VE; ++e) breg[j][e] = vs[e];
+                    for (int e = 0; e < VE; ++e) breg[j][e] = ok ? vs[e] : (Src)0.0f;
+                } else if (kb < K && u + VE <= H) {
+                    __builtin_memcpy(breg[j], src + u, 16);
                 } else {
 #pragma unroll
-                    for (int e = 0; e < VE; ++e)
-                        breg[j][e] = (kb < K && u + e < H) ? src[e] : (Src)0.0f;
+                    for (int e = 0; e < VE; ++e) breg[j][e] = (kb < K && u + e < H) ? src[u + e] : (Src)0.0f;
                 }
             }
         };
@@ -207,27 +216,25 @@ __device__ __forceinline__ void gemm_tiles(const GemmParams& p, int nrows, int r
     }
 }
 
-// Input projection: tiles of 128 x 128 x 128 bytes of K (with 64 bytes 768 tiles
-// took 100 us at D 256, with 128 85: a memory latency per block of K is in the
-// way), or where those are too few to occupy the CUs (the number of rows is
-// known here only), of 64 x 64 x 256 bytes: four times as many, with half the
-// latencies in a row each.  Which: see launch_inproj.
-template <typename E, int MODE>
+// Input projection: tiles of 128 x 128, or where those are too few to occupy the
+// CUs (the number of rows is known here only) of 64 x 64, four times as many.
+// BKL, BKS: bytes of K per block of either; see launch_inproj.
+template <typename E, int MODE, int BKL, int BKS>
 __global__ void __launch_bounds__(G_THREADS)
 gemm_kernel(GemmParams p) {
     using S = typename E::store_t;
-    using Large = GemmTile<E, G_CM, 128>;
-    using Small = GemmTile<E, G_SMALL, 256>;
+    using Large = GemmTile<E, G_CM, BKL>;
+    using Small = GemmTile<E, G_SMALL, BKS>;
     constexpr int LDS = MODE == MODE_INPROJ && Small::LDS > Large::LDS ? Small::LDS : Large::LDS;
     __shared__ __attribute__((aligned(16))) S lds[LDS];
     if constexpr (MODE == MODE_INPROJ) {
         const int nrows = p.meta->total_rows;
         const int large = ((4 * p.H + G_CM - 1) / G_CM) * ((nrows + G_RN - 1) / G_RN);
-        if (large < p.small_below) gemm_tiles<E, MODE, G_SMALL, 256>(p, nrows, 0, lds);
-        else gemm_tiles<E, MODE, G_CM, 128>(p, nrows, 0, lds);
+        if (large <= p.small_upto) gemm_tiles<E, MODE, G_SMALL, BKS>(p, nrows, 0, lds);
+        else gemm_tiles<E, MODE, G_CM, BKL>(p, nrows, 0, lds);
     } else {
         const int row_base = p.offsets[p.t];
-        gemm_tiles<E, MODE, G_CM, 64>(p, p.offsets[p.t + 1] - row_base, row_base, lds);
+        gemm_tiles<E, MODE, G_CM, BKL>(p, p.offsets[p.t + 1] - row_base, row_base, lds);
     }
 }
 
@@ -247,14 +254,27 @@ hipError_t launch_inproj(const Dims& d, const void* x, const void* W, const floa
     p.H = d.H;
     p.a_vec = (d.D % 4 == 0) && aligned16(x);
     p.b_vec = (d.H % 4 == 0) && aligned16(W);
-    // Small tiles while there is less than one large tile per CU: 64 and 128
-    // large ones take 37 and 38 us at D 256 (61 and 62 at D 512), their four
-    // times as many small ones 18 and 24 (25 and 36); 256 the same either way;
-    // 512 take 56 us and 66.
-    p.small_below = num_cus;
+    // Small tiles while there is at most one large tile per CU (D 128: 96 large ones
+    // take 23 us, their four times as many small ones 15; 190 25 and 22; 256 27 and
+    // 24; 400 34 and 35), but only up to three quarters of that where D is five runs
+    // of 16, which the small tiles' blocks pad to eight (D 65: 190 large ones 22 and
+    // 21, 247 23 and 26).
+    const int n16 = (d.D + 15) / 16;
+    p.small_upto = n16 == 5 ? num_cus * 3 / 4 : num_cus;
+    // Bytes of K per block.  Small tiles: 256, or what D fills (D 16, 190 tiles: 22.9
+    // us with 256, 16.6 and now 13.9 with 64).  Large tiles: 64, and 128 where D fills those and H
+    // the tiles' columns (a memory latency per block is in the way; 752 tiles at D
+    // 256: 104 and 89 us; 1775 at D 48, in part zeros: 63 and 74; at H 40, the
+    // second tile of columns nearly empty, D 512: 205 and 212).
+    const int ntc = (4 * d.H + G_CM - 1) / G_CM;
+    const bool wide = n16 > 2 && n16 % 2 == 0 && 8LL * ntc * G_CM <= 9 * 4LL * d.H;
     const long long tiles = (((long long)d.B * d.T + G_SMALL - 1) / G_SMALL) * ((4LL * d.H + G_SMALL - 1) / G_SMALL);
     const int grid = (int)(tiles < 4LL * num_cus ? tiles : 4LL * num_cus);
-    hipLaunchKernelGGL((gemm_kernel<EltF32, MODE_INPROJ>), dim3(grid), dim3(G_THREADS), 0, s, p);
+    auto k = n16 <= 1   ? gemm_kernel<EltF32, MODE_INPROJ, 64, 64>
+             : n16 <= 2 ? gemm_kernel<EltF32, MODE_INPROJ, 64, 128>
+             : wide     ? gemm_kernel<EltF32, MODE_INPROJ, 128, 256>
+                        : gemm_kernel<EltF32, MODE_INPROJ, 64, 256>;
+    hipLaunchKernelGGL(k, dim3(grid), dim3(G_THREADS), 0, s, p);
     return hipGetLastError();
 }
 
@@ -274,9 +294,9 @@ hipError_t launch_step_gemm(const Dims& d, int t, const void* U, const Workspace
     p.b_vec = (d.H % ve == 0) && aligned16(U);
     const int grid = ((4 * d.H + G_CM - 1) / G_CM) * ((d.B + G_RN - 1) / G_RN);
     if (d.bf16)
-        hipLaunchKernelGGL((gemm_kernel<EltH16, MODE_STEP>), dim3(grid), dim3(G_THREADS), 0, s, p);
+        hipLaunchKernelGGL((gemm_kernel<EltH16, MODE_STEP, 64, 64>), dim3(grid), dim3(G_THREADS), 0, s, p);
     else
-        hipLaunchKernelGGL((gemm_kernel<EltF32, MODE_STEP>), dim3(grid), dim3(G_THREADS), 0, s, p);
+        hipLaunchKernelGGL((gemm_kernel<EltF32, MODE_STEP, 64, 64>), dim3(grid), dim3(G_THREADS), 0, s, p);
     return hipGetLastError();
 }
 

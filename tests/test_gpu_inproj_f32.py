@@ -1,8 +1,9 @@
 """The fp32 input projection (gemm.hip) on either side of the line between its
-small and large tiles (one 128 x 128 tile of the valid rows per CU, 256 CUs) and
-at ragged edges of both: D and 4H no multiples of a block of K, a tile or a
-vector, one row, rows just past a tile.  Output sequence and final state of
-the forward against the fp64 oracle at its fp32 tolerance (1e-5)."""
+small and large tiles (one 128 x 128 tile of the valid rows per CU, 256 CUs; three
+quarters of that for D of five runs of 16), with each length of a block of K, and
+at ragged edges: D and 4H no multiples of a block of K, a tile or a vector, one
+row, rows just past a tile.  Output sequence and final state of the forward
+against the fp64 oracle at its fp32 tolerance (1e-5)."""
 import numpy as np
 import pytest
 
@@ -16,8 +17,17 @@ pytestmark = pytest.mark.gpu
 CASES = [  # D, H, B, T: large tiles
     (9, 257, 256, 14),   # 9 x 28 = 252: small
     (9, 257, 256, 15),   # 9 x 30 = 270: large
-    (68, 256, 253, 15),  # 8 x 30 = 240: small
+    (20, 256, 256, 16),  # 8 x 32 = 256: small
+    (20, 256, 241, 17),  # 8 x 33 = 264: large
+    (30, 259, 241, 17),  # 9 x 33 = 297: large
+    (68, 256, 256, 12),  # 8 x 24 = 192: small
+    (68, 256, 241, 13),  # 8 x 25 = 200: large
+    (68, 256, 253, 15),  # 8 x 30 = 240: large
     (68, 256, 241, 17),  # 8 x 33 = 264: large
+    (50, 256, 241, 17),  # 8 x 33 = 264: large, blocks of 32
+    (64, 256, 241, 17),  # the same, whole vectors
+    (97, 257, 241, 17),  # 9 x 33 = 297: large, blocks of 16, seven of them
+    (255, 130, 241, 29), # 5 x 55 = 275: large, blocks of 32
     (1, 33, 1, 1), (64, 40, 65, 1), (130, 70, 129, 2),
 ]
 
