@@ -284,14 +284,15 @@ int lstm_dyn_forward_train(lstm_dyn_t* h, const void* x, const int32_t* lengths,
  * valid steps) are products with fp32 accumulation, of fp32 operands with
  * fp32 data and of fp16 operands with bf16 data (each scaled by a power of
  * two: U per row or as a whole, the weight-gradient operands as a whole, dz
- * per row or per row and 32-column block).  Waits once or twice for copies to
- * the host (the sum of lengths, the operands' largest magnitudes).  The reverse
+ * per row or per row and 32-column block).  Waits once for copies to the host: the sum of
+ * lengths, and without the first of the loops below the step offsets and with
+ * bf16 data the largest |U|.  The reverse
  * loop of a persistent handle is one cooperative launch where U fits the CUs of
  * one XCD (B <= 256 on a 256-CU device; bf16 data: H < 1024, fp32 data: H <=
- * 512) and, with bf16 data, where H is a multiple of 256 (H <= 2048, B <=
- * 512); else two launches per step, with bf16 data (H even, 16 <= H <= 2048,
- * B <= 512) but for the steps with at most 16 rows, which are one
- * cooperative launch.  Every wait of those launches is bounded (a timeout
+ * 512) and, with bf16 data, at H = 1024 and 2048, or with more rows at 256 and
+ * 512 too (B <= 512); else two launches per step, with bf16 data (H even, 16 <=
+ * H <= 2048, B <= 512) but for the last steps where those have at most 16 rows,
+ * which are one cooperative launch.  Every wait of those launches is bounded (a timeout
  * shows in LSTM_DYN_Q_LAST_STATUS).  Consumes what the forward kept (a
  * second backward needs another forward for training).  Returns LSTM_DYN_OK,
  * ERR_INVALID (bad arguments, or no forward for training kept), ERR_HIP.
@@ -321,10 +322,11 @@ int lstm_dyn_set_option(lstm_dyn_t* h, int option, long long value);
  * the wait for the other workgroups) -- then the loop end) into
  * ticks[0 .. capacity), synchronising the forward's stream; *count receives
  * the number of entries and *khz the clock rate.  A backward pass run as
- * one launch of the whole reverse loop (bf16 data, persistent handle, H a
- * multiple of 256) records there instead, at 4 t for step t: its start, its
- * share of dh published, its cells done (the other shares awaited), the
- * marks for later steps issued; at 4 max_len the product for dh0.
+ * one launch of the whole reverse loop (LSTM_DYN_LOOP_REVERSE_GROUPED, _BLOCKS)
+ * records there instead, at 4 t for step t: its start, its product (its share
+ * of dh published) done, its cells done (the other shares awaited), the
+ * step's end (the marks for later steps issued); at 4 max_len the product for
+ * dh0.
  * Returns LSTM_DYN_OK, ERR_INVALID (option not set, NULL arguments) or ERR_HIP.
  */
 int lstm_dyn_step_trace(lstm_dyn_t* h, long long* ticks, int capacity, int* count, int* khz);

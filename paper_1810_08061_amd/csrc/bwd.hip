@@ -16,7 +16,8 @@
 //   * dh <- dz U^T for those rows, a GEMM (K = 4H) issued by the host;
 // with bf16 data on a persistent handle the steps with few rows (the last
 // ones, met first) instead run in one cooperative launch (bwd_loop_kernel,
-// below).  After the last step the weight gradients are GEMMs over all
+// below).  (Where the whole reverse loop is one launch, xbwd_kernel.h and
+// bwdblk.hip, that takes the place of both.)  After the last step the weight gradients are GEMMs over all
 // compact rows (K = sum of lengths): dW = X^T dz, dU = H_prev^T dz,
 // dx = dz W^T, and db = dz^T 1 a column sum, in gate-interleaved columns,
 // permuted back to the caller's gate blocks at the end.  dW and dU are one

@@ -1,5 +1,6 @@
 // bwdblk.hip -- the whole reverse loop of the backward pass in one cooperative
-// launch, for bf16 data on persistent handles with H a multiple of 256.
+// launch, for bf16 data on persistent handles with H 1024 or 2048, or 256 or 512
+// and more rows than the grouped loop (xbwd_kernel.h) holds.
 //
 // Backpropagation through the masked loop of the paper's Section 9 "RNN
 // cells" experiment.  Going back from the last step, the rows of step t are

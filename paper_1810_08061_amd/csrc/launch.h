@@ -186,7 +186,7 @@ hipError_t launch_bwd_loop(const Dims& d, const _Float16* u16, float alpha_u, co
                            const float* save_c, const float* dseq, float* dH, float* dC,
                            _Float16* dzx, float* dzs, unsigned* bar, unsigned long long timeout_ticks,
                            int t_end, const Workspace& ws, hipStream_t s);
-// bf16 data, H a multiple of 256 (at most 2048): the whole reverse loop in one
+// bf16 data, H 256, 512, 1024 or 2048: the whole reverse loop in one
 // cooperative launch (H / 8 workgroups, each with a 32-unit x H-column block
 // of U in registers; per step the blocks' shares of dh = dz U^T, then the
 // cell's backward of 8 units, each exchange polled for, no grid barrier),

@@ -18,16 +18,18 @@ static const XBVariant* find_xbvariant(int bf16, int H, int rg) {
 }
 
 // Whole training steps (MI355X, the path before and this one; the forward, which
-// gained 50 to 250 us of it, included):
-//   fp32 H 256, 32 rows, 100 steps    1381 and 545 us (two launches per step)
-//   fp32 H 512, 64 rows, 100 steps    2314 and 893 us
-//   bf16 H 512, 64 rows, 200 steps    1902 and 1030 us (the whole-loop launch)
-//   bf16 H 768, 128 rows, 100 steps   2539 and 1292 us (two launches per step)
-//   GRU bf16 H 750, 37 rows, 61 steps 1361 and 779 us
+// gained 50 to 250 us of it, included; lengths uniform but where full):
+//   fp32 H 256, D 256, 32 rows, 100 steps        1201 and 407 us (two launches per step)
+//   fp32 H 512, D 512, 64 rows, 100 full steps   2616 and 1294 us
+//   bf16 H 512, D 512, 64 rows, 200 steps        1710 and 854 us (the whole-loop launch)
+//   bf16 H 768, D 512, 128 rows, 100 full steps  3206 and 1488 us (two launches per step)
+//   GRU bf16 H 750, D 200, 37 rows, 61 steps     1228 and 637 us
 // In bf16 beyond H = 512 the 64 KB of dz per row tile that every CU reads, and
-// spills of the U block, cost more than the whole-loop launch's second exchange
-// (H 1024, 64 rows, 200 steps: 2170 against 2416 us), so that launch keeps the
-// sizes that it takes there (multiples of 256).
+// spills of the U block (55 to 64 registers with one row tile, 115 to 135 with
+// two), cost more than the whole-loop launch's second exchange (H 1024, D 512,
+// 200 steps, that launch and this one: 8 rows 1413 and 1729 us, 64 rows 1836 and
+// 2178, 256 rows 4106 and 5549), so that launch keeps the one size there that
+// both take (H 1024; of the multiples of 256 below it is compiled for 256 and 512).
 bool xbwd_pick(const Dims& d, int num_cus, XBwdConfig* xb) {
     *xb = XBwdConfig{};
     int shift = 3;

@@ -34,8 +34,8 @@ static xloop_fn xloop_of(const XLoopConfig& xc, int cell, int mode) {
 // fp32 H 512, 1 row 314 and 248 us, 8 rows 315 and 269, 16 rows 321 and 268, 64
 // rows 527 and 374; H 385, 8 rows 304 and 259; bf16 H 513, 8 rows 259 and 225,
 // 24 rows 320 and 231.  The one place where it is not faster is bf16 beyond H =
-// 768 with up to 16 rows, where the two are within 3% of each other (H 1024, 8
-// rows: 260 and 269; with termination 303 and 297, GRU 258 and 247, a training
+// 768 with up to 16 rows, where the two are within 4% of each other (H 1024, 8
+// rows: 260 and 269 us; with termination 303 and 297, GRU 258 and 247, a training
 // step 979 and 882).
 bool xloop_pick(const Dims& d, int num_cus, XLoopConfig* xc) {
     *xc = XLoopConfig{};

@@ -41,11 +41,11 @@
 // bytes, so a group's ring takes no room for rows that it does not have.
 //
 // Measured (MI355X, whole forward, the device-wide loop and this one):
-//   fp32 H 256, 32 rows, 100 steps         293 and 180 us
-//   fp32 H 256, 128 full rows, 128 steps   806 and 245 us (with the sequence)
-//   bf16 H 512, 64 rows, 200 steps         513 and 311 us
-//   bf16 H 1024, 128 rows, 500 steps      1202 and 1031 us (most steps a few rows)
-//   bf16 H 1024, 64 rows, 256 steps, stop  870 and 624 us
+//   fp32 H 256, 32 rows, 100 steps         292 and 160 us
+//   fp32 H 256, 128 full rows, 128 steps   814 and 242 us (with the sequence)
+//   bf16 H 512, 64 rows, 200 steps         506 and 303 us
+//   bf16 H 1024, 128 rows, 500 steps      1201 and 1034 us (most steps a few rows)
+//   bf16 H 1024, 64 rows, 256 steps, stop  858 and 632 us
 // What bounds a step now (H = 512, 1.3 us): the store's and the load's way
 // through L2 (about 0.55 us with the wait's granularity), then 16 MFMAs, the
 // partial sums through LDS and the barrier (0.4), then the gates (0.3).

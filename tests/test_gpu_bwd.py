@@ -123,8 +123,8 @@ def test_backward_large_workload_sub_batch(mode):
     """large2048_bf16 at its full shape (D 1024, H 2048, T_max 1000) on 20 rows
     spread over its length range (the longest, 1000 steps, and the shortest
     included), run on their own handle: every gradient against the oracle.
-    On the persistent handle the whole reverse loop is one launch (bf16 data,
-    H a multiple of 256), with the carried gradients held in LDS."""
+    On the persistent handle the whole reverse loop is one launch with column
+    blocks of U, the carried gradients held in LDS."""
     import torch
     name = "large2048_bf16"
     full = workloads.workload_inputs(name)

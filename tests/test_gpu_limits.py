@@ -121,7 +121,7 @@ def test_largest_per_step_batch():
 @pytest.mark.parametrize("dt,H", [("bf16", 256), ("f32", 256), ("bf16", 2048)])
 def test_largest_persistent_batch_backward(dt, H):
     """The backward at 512 rows, most of them short (steps 3 to 5 have at
-    most 16 rows): with bf16 data and H a multiple of 256 the persistent
+    most 16 rows): with bf16 data and H 256 or 2048 the persistent
     handle runs the whole reverse loop in one launch with column blocks of U,
     at its largest batch, with the carried gradients in memory rather than
     LDS (more than 256 padded rows), at the smallest and the largest U block
