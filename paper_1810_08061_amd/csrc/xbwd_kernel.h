@@ -17,9 +17,12 @@
 // So a step is one exchange.  (The whole-loop launch of bwdblk.hip splits the
 // columns over four workgroups instead, because no CU holds 4H columns of
 // enough units at H = 2048, and pays a second exchange of partial sums; all of
-// it through memory.)  With MTU = 1 the cell waves are four waves of their own,
-// which load z and the saved state two steps ahead; with MTU = 2 (H > 512, U
-// takes 128 registers of every wave) the eight waves do both.
+// it through memory.)  The cell waves are four waves of their own, which load z
+// and the saved state two steps ahead (and wait, as the gate waves there do, for
+// all that they have in flight before the cell's backward and before publishing);
+// where U leaves no registers for a third wave per SIMD (bf16 data H > 512, 128
+// registers of every wave; fp32 data H > 256, 64 beside a tile's 64 columns) the
+// eight waves do both.
 //
 // dz is exchanged in the operand type: fp32 with fp32 data; with bf16 data
 // fp16, each row's 8 units by 4 gates scaled by the power of two that brings
